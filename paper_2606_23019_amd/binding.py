@@ -327,7 +327,7 @@ def resize_mask(mask_bits, n_kb, n_qb_out, n_kb_out, stream=None):
         m = m.view(torch.int64)
     H, n_qb, _ = m.shape
     _mask_words(m, H, n_qb, n_kb)
-    out = torch.full((H, n_qb_out, (n_kb_out + 63) // 64), -1, dtype=torch.int64, device=m.device)
+    out = torch.empty((H, n_qb_out, (n_kb_out + 63) // 64), dtype=torch.int64, device=m.device)
     st = lib.sa_resize_mask(_dev_ptr(m, torch.int64, "mask_bits"), H, n_qb, n_kb,
                             _dev_ptr(out, torch.int64, "mask_out"), n_qb_out, n_kb_out,
                             _stream(stream))

@@ -70,3 +70,37 @@ def test_resize_commutes_with_instantiation_on_gpu():
     rhs = torch.stack([binding.resize_mask(masks[i], a.n_kb, b.n_qb, b.n_kb) for i in range(3)])
     torch.cuda.synchronize()
     assert torch.equal(lhs, rhs)
+
+
+UPSCALE_EDGES = [
+    # (H, nq, nk, tq, tk, seed): the upscaling kernels at their edges
+    (2, 15, 64, 15, 64, 20),     # equal sizes: one strip of 15 rows, one word
+    (2, 15, 64, 16, 65, 21),     # a second strip of one row, a second word of one column
+    (1, 30, 95, 31, 96, 22),     # strips over 16 base rows; words over three 32-bit base words
+    (3, 29, 128, 30, 129, 23),   # the last strip ends on the last base row
+    (1, 7, 33, 150, 1030, 24),   # every target row of a strip on one or two base rows
+    (3, 50, 511, 61, 513, 25),   # one column past eight wavefronts; ragged base word
+    (5, 9, 2, 13, 700, 26),      # 65 target rows: one past a wavefront of rows
+    (1, 12, 40, 5, 90, 27),      # fewer rows, more columns
+    (1, 12, 90, 40, 40, 28),     # more rows, fewer columns
+]
+
+
+@pytest.mark.parametrize("H,nq,nk,tq,tk,seed", UPSCALE_EDGES)
+def test_upscale_edges_bit_exact(H, nq, nk, tq, tk, seed):
+    torch = _torch()
+    from paper_2606_23019_amd import binding
+    rng = np.random.default_rng(seed)
+    T = rng.standard_normal((H, nq, nk)).astype(np.float32)
+    T.reshape(-1)[::13] = np.nan
+    T.reshape(-1)[5::29] = np.inf
+    T.reshape(-1)[7::31] = -np.inf
+    got = binding.resize_threshold_map(torch.from_numpy(T).cuda(), tq, tk)
+    assert np.array_equal(got.cpu().numpy(), ors.resize_threshold_map(T, tq, tk), equal_nan=True)
+    M = rng.random((H, nq, nk)) < 0.3
+    packed = pack_rows(M)
+    if nk % 64:
+        packed[..., -1] |= ~np.uint64((1 << (nk % 64)) - 1)  # bits past the last block are ignored
+    bits = binding.resize_mask(packed, nk, tq, tk)
+    assert np.array_equal(bits.cpu().numpy().view(np.uint64),
+                          oracle.pack_crm(ors.resize_mask(M, tq, tk)))
