@@ -14,6 +14,8 @@
 // bytes read per block, one bit written per block and threshold, three vector
 // instructions per 64 bits (the compare and two lane writes).
 
+#include <algorithm>
+
 #include "device_common.h"
 #include "launch.h"
 
@@ -92,12 +94,162 @@ __global__ __launch_bounds__(64 * kInstWaves) void mask_inst_kernel(
   }
 }
 
+// Many thresholds.  The comparisons bound the call: one vector compare per 64
+// blocks and threshold at least, and in the kernel above two lane writes and
+// their wait beside it, since a ballot is a scalar and stores take lanes.  Here
+// a lane owns 32 consecutive blocks of a row (their map entries stay in
+// registers for every threshold) and builds its half word by itself, a compare
+// and an add-with-carry per block: acc = 2 acc + (t <= p).  That is two
+// instructions per 64 blocks and threshold instead of five issue slots, at the
+// price of a way through LDS for the map entries, so it takes sets of at least
+// kInstManyMin thresholds.  Half words of consecutive lanes are consecutive in
+// memory, whatever rows and heads they belong to; a lane reads its own head's
+// threshold.  40 x 591^2 maps, 50 thresholds: 98.4 -> 63 us, of which the
+// comparisons alone are 46 us; without the early requests 67 us (all
+// wavefronts load, then all compare).
+constexpr int kInstManyMin = 6;
+constexpr int kInstManyWaves = 4;
+constexpr int kInstManyResident = 4;  // wavefronts a SIMD
+
+// For k = 15 .. 0: acc = 2 acc + (t[k] <= p).  One statement, so that nothing
+// is put between the pairs.
+__device__ __forceinline__ void push16(uint32_t& acc, const float* t, float p) {
+#define SA_PUSH(n) "v_cmp_le_f32 vcc, %" #n ", %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+  asm(SA_PUSH(17) SA_PUSH(16) SA_PUSH(15) SA_PUSH(14) SA_PUSH(13) SA_PUSH(12) SA_PUSH(11)
+          SA_PUSH(10) SA_PUSH(9) SA_PUSH(8) SA_PUSH(7) SA_PUSH(6) SA_PUSH(5) SA_PUSH(4) SA_PUSH(3)
+              SA_PUSH(2)
+      : "+v"(acc)
+      : "v"(p), "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]),
+        "v"(t[7]), "v"(t[8]), "v"(t[9]), "v"(t[10]), "v"(t[11]), "v"(t[12]), "v"(t[13]),
+        "v"(t[14]), "v"(t[15])
+      : "vcc");
+#undef SA_PUSH
+}
+
+// Where lane l's half word f is in the map.
+struct HalfWord {
+  int64_t at;  // first entry of its 32
+  int head;
+  int down;  // places it is shifted down by
+};
+
+__device__ __forceinline__ HalfWord half_word(int64_t f, int n_qb, int n_kb, int W) {
+  const int row = (int)(f / (2 * W));
+  const int v0 = (int)(f - (int64_t)row * (2 * W)) * 32;  // first block of the half word
+  // the 32 entries end with the row at the latest (n_kb >= 32); the half word
+  // of a lane moved back so is shifted down again, which drops the entries of
+  // earlier half words and leaves zeros past the row's end
+  const int from = min(v0, n_kb - 32);
+  return HalfWord{(int64_t)row * n_kb + from, row / n_qb, v0 - from};
+}
+
+// A wavefront takes groups of 64 half words g, g + n_waves, ... (with n_parts
+// parts of the thresholds each) and requests the next one's entries before it
+// compares, so that only the first group's loads are waited for.
+__global__ __launch_bounds__(64 * kInstManyWaves) void mask_inst_many_kernel(
+    const float* __restrict__ T, const float* __restrict__ p, int n_p, int per_part, int n_parts,
+    int H, int n_qb, int n_kb, int W, uint32_t* __restrict__ bits) {
+  // a wavefront's entries on their way from memory order to lane order, half
+  // of each lane's at a time, in rows of 20 floats (16 lanes' 16-byte reads
+  // lie in different banks); then the lanes' thresholds
+  __shared__ __attribute__((aligned(16))) float stage_all[kInstManyWaves][64][20];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float(*stage)[20] = stage_all[wave];
+  const int64_t n_half = (int64_t)H * n_qb * (2 * W);
+  const int64_t n_units = (n_half + 63) / 64 * n_parts;
+  const int64_t n_waves = (int64_t)gridDim.x * kInstManyWaves;
+  int64_t unit = (int64_t)blockIdx.x * kInstManyWaves + wave;
+  if (unit >= n_units) return;  // uniform; no workgroup barrier below
+
+  // four lanes read 64 bytes of one half word's entries, 16 half words a load
+  f32x4 x[2][4];
+  HalfWord hw;
+  int64_t f;
+  auto request = [&](int64_t un) {
+    f = min(un / n_parts * 64 + lane, n_half - 1);  // lanes past the end repeat the last
+    hw = half_word(f, n_qb, n_kb, W);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int64_t src = __shfl(hw.at, 16 * j + (lane >> 2), 64) + 4 * (lane & 3);
+      __builtin_memcpy(&x[0][j], T + src, 16);  // 4-byte aligned
+      __builtin_memcpy(&x[1][j], T + src + 16, 16);
+    }
+  };
+  request(unit);
+  while (true) {
+    const int i0 = (int)(unit % n_parts) * per_part;
+    const int i1 = min(n_p, i0 + per_part);
+    const float* ph = p + hw.head;
+    const int down = hw.down;
+    uint32_t* o = bits + (int64_t)i0 * n_half + f;
+    float t[32];
+#pragma unroll
+    for (int k0 = 0; k0 < 2; ++k0) {
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        *(SA_LDS f32x4*)&stage[16 * j + (lane >> 2)][4 * (lane & 3)] = x[k0][j];
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+#pragma unroll
+      for (int k = 0; k < 16; k += 4) {
+        const f32x4 y = *(const SA_LDS f32x4*)&stage[lane][k];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[16 * k0 + k + e] = y[e];
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    }
+    // The lanes' thresholds take the stage's place, kStaged settings at a
+    // time: read from memory inside the loop, each would wait for the store
+    // before it (one counter for both), and LDS reads do not.
+    constexpr int kStaged = 20;
+    float* lane_p = &stage[0][0] + lane;
+    const int64_t next = unit + n_waves;
+    for (int c0 = i0; c0 < i1; c0 += kStaged) {
+      const int n = min(kStaged, i1 - c0);
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll 4
+      for (int i = 0; i < n; ++i) lane_p[64 * i] = ph[(int64_t)(c0 + i) * H];
+      if (c0 + kStaged >= i1 && next < n_units) request(next);
+      float pn = lane_p[0];
+      for (int i = 0; i < n; ++i) {
+        const float pi = pn;
+        pn = lane_p[64 * min(i + 1, n - 1)];
+        uint32_t acc = 0;
+        push16(acc, t + 16, pi);
+        push16(acc, t, pi);
+        *o = down < 32 ? acc >> (down & 31) : 0u;  // lanes past the end: the last one's, again
+        o += n_half;
+      }
+    }
+    if (next >= n_units) break;
+    unit = next;
+  }
+}
+
 }  // namespace
 
 hipError_t launch_mask_instantiate(const float* T, const float* p, int n_p, int H, int n_qb,
                                    int n_kb, uint64_t* bits, hipStream_t stream) {
   const int64_t rows = (int64_t)H * n_qb;
   const int W = (n_kb + 63) / 64;
+  if (n_p >= kInstManyMin && n_kb >= 32) {
+    const int64_t groups = (rows * (2 * W) + 63) / 64;
+    const int64_t places = 4 * 256 * kInstManyResident;
+    // a group's thresholds are cut in parts until there are several units for
+    // every place on the chip, but not below kInstManyMin
+    const int64_t cuts = std::min<int64_t>(std::max<int64_t>(1, 4 * places / groups),
+                                           n_p / kInstManyMin);
+    const int per_part = (int)((n_p + cuts - 1) / cuts);
+    const int n_parts = (n_p + per_part - 1) / per_part;
+    const int64_t waves = std::min<int64_t>(groups * n_parts, places);
+    hipLaunchKernelGGL(mask_inst_many_kernel,
+                       dim3((unsigned)((waves + kInstManyWaves - 1) / kInstManyWaves)),
+                       dim3(64 * kInstManyWaves), 0, stream, T, p, n_p, per_part, n_parts, H, n_qb,
+                       n_kb, W, (uint32_t*)bits);
+    return hipGetLastError();
+  }
   const int64_t grid = (rows + kInstWaves - 1) / kInstWaves;
   const int chunks = (n_p + kInstThr - 1) / kInstThr;
   if (chunks > 65535) return hipErrorInvalidValue;

@@ -62,6 +62,35 @@ def test_instantiate_ties_nan_and_extremes():
     assert np.array_equal(got, oracle.instantiate_packed(T, p))
 
 
+MANY = [
+    # (H, n_qb, n_kb, n_p, seed): sets that the many-threshold kernel takes, at its edges
+    (1, 1, 32, 6, 20),      # one half word with entries and one without
+    (3, 7, 31, 6, 21),      # rows too short for it
+    (3, 7, 33, 7, 22),      # a half word of one block, read from 31 blocks earlier
+    (5, 13, 95, 20, 23),    # one staged chunk of thresholds; heads change inside a wavefront
+    (40, 2, 64, 21, 24),    # a chunk and one more; a head every four half words
+    (2, 33, 97, 64, 25),    # a half word past the row's end that reads none of its entries
+    (4, 256, 300, 9, 26),   # sets cut in no parts
+    (16, 591, 591, 13, 27),  # several groups a wavefront
+]
+
+
+@pytest.mark.parametrize("H,n_qb,n_kb,n_p,seed", MANY)
+def test_instantiate_many_thresholds_bit_exact(H, n_qb, n_kb, n_p, seed):
+    rng = np.random.default_rng(seed)
+    T = rng.integers(-4, 5, size=(H, n_qb, n_kb)).astype(np.float32)  # ties with p, and -0 below
+    T.reshape(-1)[::7] *= -1.0
+    T.reshape(-1)[3::11] = np.nan
+    T.reshape(-1)[5::17] = np.inf
+    T.reshape(-1)[6::19] = -np.inf
+    T.reshape(-1)[2::23] = 1e-42
+    p = rng.integers(-4, 5, size=(n_p, H)).astype(np.float32)
+    p.reshape(-1)[::5] *= -1.0
+    p.reshape(-1)[1::9] = np.nan
+    p.reshape(-1)[2::13] = np.inf
+    assert np.array_equal(_run(T, p), oracle.instantiate_packed(T, p))
+
+
 def test_instantiate_full_720p_maps():
     # 14B-720p shape: 40 heads of 591 x 591 blocks, per-head densities, 4 timesteps
     wl = WAN14B_720P
