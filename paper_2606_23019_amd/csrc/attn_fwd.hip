@@ -494,6 +494,98 @@ struct PingPong {
 template <int BQ, int BK, int D, bool DENSE>
 constexpr bool kUsePingPong = PingPong<BQ, BK, D>::kFits && (BQ == 128 || DENSE);
 
+// Puts together the PARTS parts of the workgroup's shared items: maxima, sums
+// and accumulators of parts 1 .. go through LDS into those of part 0, which
+// end up as the item's.  Every wavefront of the workgroup calls this, when the
+// K and V tiles (KV bytes each) are free; `wave` numbers the WAVES wavefronts
+// of a part, and equal lanes of equal wavefronts hold the same elements.  The
+// accumulators take WAVES (PARTS - 1) times 128 D bytes; maxima and sums go
+// behind them, or ahead of them in a round of their own where the tiles are
+// too small for both.
+template <int PARTS, int WAVES, int D, int KV>
+__device__ __forceinline__ void merge_parts(f32x16 (&o)[D / 32], float& m, float& l, char* k_tiles,
+                                            char* v_tiles, int part, int wave, int lane) {
+  constexpr int kWaveBytes = 32 * D * 4;
+  constexpr int kSums = (PARTS - 1) * WAVES * kWaveBytes;
+  constexpr int kStats = (PARTS - 1) * WAVES * 512;
+  static_assert(kSums <= 2 * KV && kStats <= KV && KV % kWaveBytes == 0, "the tiles hold the parts");
+  constexpr bool kOneRound = kSums + kStats <= 2 * KV;
+  auto at = [&](int off) { return off < KV ? k_tiles + off : v_tiles + (off - KV); };
+  auto stats = [&](int p) {
+    return (SA_LDS float*)(SA_LDS void*)(at((kOneRound ? kSums : 0) + ((p - 1) * WAVES + wave) * 512) +
+                                         lane * 8);
+  };
+  auto sums = [&](int p) { return at(((p - 1) * WAVES + wave) * kWaveBytes) + lane * 16; };
+  auto write_sums = [&]() {
+#pragma unroll
+    for (int i = 0; i < D / 8; ++i)
+      *(SA_LDS f32x4*)(sums(part) + i * 1024) =
+          f32x4{o[i / 4][4 * (i % 4)], o[i / 4][4 * (i % 4) + 1], o[i / 4][4 * (i % 4) + 2],
+                o[i / 4][4 * (i % 4) + 3]};
+  };
+  if (part > 0) {
+    stats(part)[0] = m;
+    stats(part)[1] = l;
+    if (kOneRound) write_sums();
+  }
+  barrier_lds_reads_done();
+  float scale[PARTS];
+  if (part == 0) {
+    float mp[PARTS], lp[PARTS];
+    mp[0] = m;
+    lp[0] = l;
+#pragma unroll
+    for (int p = 1; p < PARTS; ++p) {
+      mp[p] = stats(p)[0];
+      lp[p] = stats(p)[1];
+      m = fmaxf(m, mp[p]);
+    }
+    // A part whose maximum is -inf (no key blocks, or nothing but logits of
+    // -inf) adds nothing to one that has a finite one: its sums may be NaN.
+    l = 0.f;
+#pragma unroll
+    for (int p = 0; p < PARTS; ++p) {
+      const bool none = mp[p] == -INFINITY && m != -INFINITY;
+      scale[p] = mp[p] == m ? 1.f : none ? 0.f : fast_exp2(mp[p] - m);
+      l += none ? 0.f : scale[p] * lp[p];
+    }
+  }
+  if (!kOneRound) {
+    barrier_lds_reads_done();
+    if (part > 0) write_sums();
+    barrier_lds_reads_done();
+  }
+  if (part == 0) {
+#pragma unroll
+    for (int dg = 0; dg < D / 32; ++dg)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) o[dg][e] = scale[0] == 0.f ? 0.f : o[dg][e] * scale[0];
+#pragma unroll
+    for (int p = 1; p < PARTS; ++p)
+#pragma unroll
+      for (int i = 0; i < D / 8; ++i) {
+        const f32x4 x = *(const SA_LDS f32x4*)(sums(p) + i * 1024);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          o[i / 4][4 * (i % 4) + e] =
+              scale[p] == 0.f ? o[i / 4][4 * (i % 4) + e]
+                              : fmaf(scale[p], x[e], o[i / 4][4 * (i % 4) + e]);
+      }
+  }
+  barrier_lds_reads_done();  // the tiles are free again
+}
+
+// Whether S requests the K operands of step dc + 1 before the MFMAs of step dc.
+// Left to itself the compiler reads each pair just before its use, and every
+// pair waits for LDS: an MFMA phase alone on a compute unit takes 3134 cycles
+// (128 x 128, d = 128; its 64 MFMAs are 2048), 2712 with the early requests.
+// Beside another group's softmax it is 3195 -> 3113, +1.4 % maskless; with
+// masks and a full chip, clocked down by its power, it measured -1 to +0.5 %
+// and the plain form stays.  Items of 64 rows have no registers to spare: at
+// d = 64 it would cost them the second workgroup of a compute unit.
+template <int BQ, bool DENSE, int PARTS>
+constexpr bool kReadAhead = BQ == 128 && (DENSE || PARTS > 1);
+
 // Ping-pong kernel.  An 8-wavefront workgroup runs 2 items of 128 query rows
 // (or 4 of 64): wavefronts 0-3 and 4-7 form two groups, each item with its
 // own K and V tiles in LDS (128 KB at 128 x 128, d = 128: one workgroup per
@@ -511,269 +603,93 @@ constexpr bool kUsePingPong = PingPong<BQ, BK, D>::kFits && (BQ == 128 || DENSE)
 // workgroup's items, idle where its own item has no block, plus one offset
 // barrier.  The items are neighbours in one XCD's sequence of the schedule,
 // so they share most key blocks and have similar counts.
+//
+// PARTS > 1 (bsattn_split_kernel): kItems / PARTS items a workgroup, each
+// shared by PARTS slots that take its key blocks in PARTS runs, put together at
+// the end (merge_parts).  For problems with fewer items than the chip has
+// places, see parts_of().  The two kernels have one body, included as text: as
+// an inlined function it was scheduled otherwise (V operands read only when
+// they are needed) and ran up to 5 % slower.
+#define SA_PP_PARAMS                                                                              \
+  const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K, const __bf16 *__restrict__ V,       \
+      const int32_t *__restrict__ counts, const int32_t *__restrict__ lists,                      \
+      const int32_t *__restrict__ order, OutT *__restrict__ O, float *__restrict__ LSE, int H,    \
+      int N, int n_qb, int n_kb, float c_log2, int64_t sb, int64_t sh, int sn, int n_items
+
 template <int BQ, int BK, int D, bool DENSE, typename OutT>
-__global__ __launch_bounds__(512, 1) void bsattn_fwd_pp_kernel(
-    const __bf16* __restrict__ Q, const __bf16* __restrict__ K, const __bf16* __restrict__ V,
-    const int32_t* __restrict__ counts, const int32_t* __restrict__ lists,
-    const int32_t* __restrict__ order, OutT* __restrict__ O, float* __restrict__ LSE, int H,
-    int N, int n_qb, int n_kb, float c_log2, int64_t sb, int64_t sh, int sn, int n_items) {
-  using T = Tile<BQ, BK, D>;
-  constexpr int kItems = PingPong<BQ, BK, D>::kItems;  // items per workgroup
-  __shared__ __attribute__((aligned(1024))) __bf16 Ks_all[kItems][BK * D];
-  __shared__ __attribute__((aligned(1024))) __bf16 Vs_all[kItems][BK * D];
+__global__ __launch_bounds__(512, 1) void bsattn_fwd_pp_kernel(SA_PP_PARAMS) {
+  constexpr int PARTS = 1;
+#include "attn_pp_body.h"
+}
 
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int grp = __builtin_amdgcn_readfirstlane(wave >> 2);
-  const int slot = __builtin_amdgcn_readfirstlane(wave / T::kWaves);  // this wave's item
-  const int gwave = wave % T::kWaves;  // wavefront inside its item
-  const int half = lane >> 5;
-  const int l32 = lane & 31;
-  __bf16* Ks = Ks_all[slot];
-  __bf16* Vs = Vs_all[slot];
+template <int BQ, int BK, int D, bool DENSE, typename OutT, int PARTS>
+__global__ __launch_bounds__(512, 1) void bsattn_split_kernel(SA_PP_PARAMS) {
+#include "attn_pp_body.h"
+}
+#undef SA_PP_PARAMS
 
-  // Workgroup b on XCD b mod 8 takes items kItems (b / 8) .. + kItems - 1 of
-  // that XCD's sequence: the launch positions x + 8 j of the one-item layout.
-  auto pos_of = [&](int sl) -> int64_t {
-    return (int64_t)(blockIdx.x % kXcds) + kXcds * (kItems * (int64_t)(blockIdx.x / kXcds) + sl);
+// Parts that an item of n_kb key blocks (where all are on) is shared in, for
+// XCD sequences of up to `seq` items.  An XCD has kCus compute units with one
+// ping-pong workgroup each, of two items of 128 query rows or four of 64
+// (masked items of 64 rows: up to four workgroups of one).  A problem that
+// does not fill them leaves units and groups idle, so its items are shared by
+// the groups of a workgroup instead, as many to an item as there are compute
+// units for.  The rule goes by the shape alone, so that every entry point and
+// order gives the same bits.  Measured, d = 128, start -> shared, us:
+//   128 x 128, two parts: maskless 1 head x 16000 tokens 332 -> 175, 2 x 16000
+//   337 -> 236; masked 2 x 8000 132 -> 75, 3 x 2000 39 -> 24;
+//   64 x 64, four: maskless 1 x 16000 429 -> 156, masked 64 -> 32; two: 4 x
+//   8000 228 -> 149 and 132 -> 98.
+// One item a workgroup without sharing it gained 5-10 %; past the line sharing
+// would cost two rounds of halves for one of pairs.  Short rows have little to
+// share: four parts of 16 blocks at 0.3 density took 8.4 us for 7.7.
+constexpr int kCus = 32;  // compute units of an XCD
+
+inline int parts_of(int64_t seq, int slots, int n_kb) {
+  int parts = n_kb >= 8 ? slots : 1;
+  while (parts > 1 && seq * parts > kCus * slots) parts /= 2;
+  return parts;
+}
+
+template <int BQ, int BK, int D, bool DENSE, typename OutT, int PARTS>
+hipError_t launch_pp(const AttnArgs& a, int64_t n_items, int64_t seq, hipStream_t stream) {
+  // consecutive items of one XCD's sequence per workgroup
+  constexpr int kItems = PingPong<BQ, BK, D>::kItems / PARTS;
+  const int64_t n_wg = kXcds * ((seq + kItems - 1) / kItems);
+  auto args = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(512), 0, stream, (const __bf16*)a.q,
+                       (const __bf16*)a.k, (const __bf16*)a.v, a.counts, a.lists, a.order,
+                       (OutT*)a.out, a.lse, a.H, a.N, a.n_qb, a.n_kb, a.scale * kLog2e, a.sb, a.sh,
+                       a.sn, (int)n_items);
   };
-  // The look-ups are branch-free (positions clamped, validity applied after
-  // the loads), so that the scalar loads of all items go out together:
-  // every order entry, then every count and this item's first key block, in
-  // two rounds of memory latency instead of one chain per item.
-  int it_of[kItems];
-#pragma unroll
-  for (int sl = 0; sl < kItems; ++sl) {
-    const int64_t pos = min(pos_of(sl), (int64_t)n_items - 1);
-    if (DENSE) {
-      int uu;
-      const int unit = xcd_slice(pos, n_items / n_qb, n_qb, &uu);
-      it_of[sl] = min(max(unit * n_qb + uu, 0), n_items - 1);
-    } else {
-      it_of[sl] = order[pos];
-    }
-  }
-  __builtin_amdgcn_sched_barrier(0);  // all order loads issued before any is used
-  int c_of[kItems];
-  int item = 0;
-#pragma unroll
-  for (int sl = 0; sl < kItems; ++sl) {
-    const int it = min(max(it_of[sl], 0), n_items - 1);
-    c_of[sl] = DENSE ? n_kb : counts[(it / n_qb) % H * n_qb + it % n_qb];
-    if (sl == slot) item = it;
-  }
-  const int bh = item / n_qb;
-  const int u = item - bh * n_qb;
-  const int h = bh % H;
-  const int row = h * n_qb + u;
-  const int32_t* list = DENSE ? nullptr : lists + (int64_t)row * n_kb;
-  auto kblk = [&](int t) { return DENSE ? t : min(max(list[t], 0), n_kb - 1); };
-  int first = kblk(0);  // in range for every row (n_kb >= 1): read before cnt is known
-  asm volatile("" : "+s"(first));     // keeps that load here, not inside the cnt > 0 branch
-  __builtin_amdgcn_sched_barrier(0);  // counts and the first key block issued together
-  // every item's count: all groups run max(counts) iterations
-  int cnt = 0, n_iter = 0;
-#pragma unroll
-  for (int sl = 0; sl < kItems; ++sl) {
-    const int c = pos_of(sl) < n_items ? min(max(c_of[sl], 0), n_kb) : 0;
-    n_iter = max(n_iter, c);
-    if (sl == slot) cnt = c;
-  }
-  const bool has_item = pos_of(slot) < n_items;
-
-  const int64_t base = (int64_t)(bh / H) * sb + (int64_t)h * sh;
-  const __bf16* Qb = Q + base;
-  const __bf16* Kb = K + base;
-  const __bf16* Vb = V + base;
-
-  const int gwave_u = __builtin_amdgcn_readfirstlane(gwave);
-  CopyPlan<T, D> cp;
-  cp.init(gwave_u, lane, sn);
-  if (cnt > 0) issue_tile_copy<T, BK, D>(Ks, Kb, first * BK, N, sn, gwave_u, lane, cp);
-
-  // Q^T fragments (B operand): lane holds Q[row gwave 32 + l32 of the item]
-  // [16 dc + 8 half .. +7].  With square tiles the item's Q rows come in as
-  // one more tile copy, into its V tile (free until the first softmax phase
-  // issues V[0]), and are read from there after the barriers below: rows of
-  // 256 contiguous bytes per four lanes instead of 32 rows per load
-  // instruction.  In a ragged last query block, rows past N hold row N - 1
-  // (their outputs are not stored); a workgroup slot without an item copies
-  // the clamped item's rows and stores nothing.
-  constexpr bool kStageQ = BQ == BK;
-  const int qrow = u * BQ + gwave * 32 + l32;
-  bf16x8 qf[D / 16];
-  if constexpr (kStageQ) {
-    issue_tile_copy<T, BK, D>(Vs, Qb, u * BQ, N, sn, gwave_u, lane, cp);
-  } else {
-#pragma unroll
-    for (int dc = 0; dc < D / 16; ++dc) {
-      if (has_item && qrow < N)
-        qf[dc] = *(const bf16x8*)(Qb + (int64_t)qrow * sn + dc * 16 + half * 8);
-      else
-        qf[dc] = bf16x8{};
-    }
-  }
-  __builtin_amdgcn_s_waitcnt(0xF70);  // vmcnt(0): Q and K[0] landed
-
-  f32x16 o[D / 32];
-#pragma unroll
-  for (int dg = 0; dg < D / 32; ++dg) o[dg] = f32x16{};
-  float m_run = -INFINITY;
-  float l_run = 0.f;
-  const int g = lane >> 4;
-  const int j = lane & 15;
-  bf16x8 pf[BK / 16];
-#pragma unroll
-  for (int c = 0; c < BK / 16; ++c) pf[c] = bf16x8{};
-
-  if (grp == 1) barrier_lds_reads_done();  // the second group runs one phase behind
-  barrier_lds_reads_done();                // both groups' K[0] (and Q) tiles are in LDS
-  if constexpr (kStageQ) {
-    // every wavefront's Q copy landed before the first barrier; the group's
-    // reads complete before the barrier that ends its first MFMA phase,
-    // after which its first softmax phase reuses the tile for V[0]
-    const int qr = gwave * 32 + l32;
-#pragma unroll
-    for (int dc = 0; dc < D / 16; ++dc)
-      qf[dc] = lds_read_b128(Vs + qr * D + (((2 * dc + half) ^ swz<D>(qr)) << 3));
-  }
-
-  for (int t = 0; t <= n_iter; ++t) {
-    // ---- MFMA phase: P V of block t - 1, then S of block t
-    if (t >= 1 && t - 1 < cnt) {
-#pragma unroll
-      for (int c = 0; c < BK / 16; ++c) {
-#pragma unroll
-        for (int dg = 0; dg < D / 32; ++dg) {
-          const int dd = dg * 32 + 16 * (g & 1) + (j & 3) * 4;
-          const int r0 = c * 16 + 8 * (g >> 1) + (j >> 2);
-          const int r1 = r0 + 4;
-          const bf16x4 lo = lds_read_tr16_b64(Vs + r0 * D + (((dd >> 3) ^ swz<D>(r0)) << 3) + (dd & 7));
-          const bf16x4 hi = lds_read_tr16_b64(Vs + r1 * D + (((dd >> 3) ^ swz<D>(r1)) << 3) + (dd & 7));
-          const bf16x8 a = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
-          o[dg] = mfma32x32x16(a, pf[c], o[dg]);
-        }
-      }
-    }
-    f32x16 s[BK / 32];
-#pragma unroll
-    for (int kg = 0; kg < BK / 32; ++kg) s[kg] = f32x16{};
-    const bool do_s = t < cnt;
-    if (do_s) {
-#pragma unroll
-      for (int dc = 0; dc < D / 16; ++dc) {
-#pragma unroll
-        for (int kg = 0; kg < BK / 32; ++kg) {
-          const int kr = kg * 32 + key_of_row(l32);
-          const bf16x8 a = lds_read_b128(Ks + kr * D + (((2 * dc + half) ^ swz<D>(kr)) << 3));
-          s[kg] = mfma32x32x16(a, qf[dc], s[kg]);
-        }
-      }
-    }
-    barrier_lds_reads_done();  // this group's Ks and Vs are free
-    if (t == n_iter) break;
-
-    // ---- softmax phase of block t; copies of V[t] and K[t + 1]
-    if (do_s) {
-      const int key0 = kblk(t) * BK;
-      const bool more = t + 1 < cnt;
-      issue_tile_copy<T, BK, D>(Vs, Vb, key0, N, sn, gwave_u, lane, cp);
-      if (key0 + BK > N) {
-#pragma unroll
-        for (int kg = 0; kg < BK / 32; ++kg)
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int key = key0 + kg * 32 + 16 * (i >> 3) + 8 * half + (i & 7);
-            if (key >= N) s[kg][i] = -INFINITY;
-          }
-      }
-      float mx = -INFINITY;
-#pragma unroll
-      for (int kg = 0; kg < BK / 32; ++kg)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kg][i]);
-      mx = pair_max(mx) * c_log2;
-      if (more) issue_tile_copy<T, BK, D>(Ks, Kb, kblk(t + 1) * BK, N, sn, gwave_u, lane, cp);
-      const bool grow = mx > m_run;
-      if (__any(grow)) {
-        const float m_new = grow ? mx : m_run;
-        const float alpha = fast_exp2(m_run - m_new);
-        m_run = m_new;
-        l_run *= alpha;
-#pragma unroll
-        for (int dg = 0; dg < D / 32; ++dg) o[dg] *= alpha;
-      }
-      float lsum = 0.f;
-#pragma unroll
-      for (int kg = 0; kg < BK / 32; ++kg)
-#pragma unroll
-        for (int j8 = 0; j8 < 2; ++j8)
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float p = fast_exp2(fmaf(s[kg][8 * j8 + e], c_log2, -m_run));
-            lsum += p;
-            pf[2 * kg + j8][e] = (__bf16)p;
-          }
-      l_run += lsum;
-    }
-    barrier_copies_landed<0>();  // this group's V[t] and K[t + 1] landed
-  }
-  if (grp == 0) barrier_lds_reads_done();  // matches the second group's extra barrier
-
-  const float l_tot = pair_sum(l_run);
-  const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-  const int l32_e = lane_e & 31;
-  const int half_e = lane_e >> 5;
-  const int row0 = u * BQ + gwave_u * 32;
-  if constexpr (kStagedStore<BQ, BK, D, OutT>) {
-    // every wavefront's LDS reads and copies are over (the last barrier
-    // above), so this item's K and V tiles are free: wavefront w of the item
-    // stages its rows in bytes [w S, (w + 1) S) of [Ks | Vs], S = 32 D sizeof(OutT)
-    if (has_item) {
-      if (half_e == 0 && row0 + l32_e < N)
-        LSE[(int64_t)bh * N + row0 + l32_e] = l_tot > 0.f ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
-      constexpr int kSlice = 32 * D * (int)sizeof(OutT);
-      constexpr int kTileBytes = BK * D * 2;
-      const int off = gwave_u * kSlice;
-      char* slice = off < kTileBytes ? (char*)Ks + off : (char*)Vs + (off - kTileBytes);
-      store_rows_staged<D, OutT>(o, inv, slice, O + base + (int64_t)row0 * sn, sn, N - row0, lane_e);
-    }
-  } else if (has_item && row0 + l32_e < N) {
-    if (half_e == 0)
-      LSE[(int64_t)bh * N + row0 + l32_e] = l_tot > 0.f ? (m_run + fast_log2(l_tot)) * kLn2 : -INFINITY;
-    OutT* orow = (O + base + (int64_t)row0 * sn) + (uint32_t)(l32_e * sn);
-#pragma unroll
-    for (int dg = 0; dg < D / 32; ++dg)
-#pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4)
-        store_out4(orow + dg * 32 + 8 * r4 + 4 * half_e, o[dg][4 * r4 + 0] * inv,
-                   o[dg][4 * r4 + 1] * inv, o[dg][4 * r4 + 2] * inv, o[dg][4 * r4 + 3] * inv);
-  }
+  if constexpr (PARTS == 1)
+    args(bsattn_fwd_pp_kernel<BQ, BK, D, DENSE, OutT>);
+  else
+    args(bsattn_split_kernel<BQ, BK, D, DENSE, OutT, PARTS>);
+  return hipGetLastError();
 }
 
 template <int BQ, int BK, int D, bool DENSE, typename OutT>
 hipError_t launch_tile(const AttnArgs& a, hipStream_t stream) {
   const int64_t n_items = (int64_t)a.B * a.H * a.n_qb;
+  const int64_t seq = (n_items + kXcds - 1) / kXcds;  // longest XCD sequence
+  if constexpr (PingPong<BQ, BK, D>::kFits && !(DENSE && BQ != BK)) {  // maskless blocks are square
+    constexpr int kSlots = PingPong<BQ, BK, D>::kItems;
+    const int parts = parts_of(seq, kSlots, a.n_kb);
+    if constexpr (kSlots == 4)
+      if (parts == 4) return launch_pp<BQ, BK, D, DENSE, OutT, 4>(a, n_items, seq, stream);
+    if (parts == 2) return launch_pp<BQ, BK, D, DENSE, OutT, 2>(a, n_items, seq, stream);
+  }
   if constexpr (kUsePingPong<BQ, BK, D, DENSE>) {
-    // kItems consecutive items of one XCD's sequence per workgroup
-    constexpr int kItems = PingPong<BQ, BK, D>::kItems;
-    const int64_t seq0 = (n_items + kXcds - 1) / kXcds;  // longest XCD sequence
-    const int64_t n_wg = kXcds * ((seq0 + kItems - 1) / kItems);
-    hipLaunchKernelGGL((bsattn_fwd_pp_kernel<BQ, BK, D, DENSE, OutT>), dim3((unsigned)n_wg),
-                       dim3(512), 0, stream, (const __bf16*)a.q,
-                       (const __bf16*)a.k, (const __bf16*)a.v, a.counts, a.lists, a.order,
-                       (OutT*)a.out, a.lse, a.H, a.N, a.n_qb, a.n_kb, a.scale * kLog2e, a.sb,
-                       a.sh, a.sn, (int)n_items);
+    return launch_pp<BQ, BK, D, DENSE, OutT, 1>(a, n_items, seq, stream);
   } else {
     hipLaunchKernelGGL((bsattn_fwd_kernel<BQ, BK, D, DENSE, OutT>), dim3((unsigned)n_items),
                        dim3(Tile<BQ, BK, D>::kThreads), 0, stream, (const __bf16*)a.q,
                        (const __bf16*)a.k, (const __bf16*)a.v, a.counts, a.lists, a.order,
                        (OutT*)a.out, a.lse, a.H, a.N, a.n_qb, a.n_kb, a.scale * kLog2e, a.sb,
                        a.sh, a.sn);
+    return hipGetLastError();
   }
-  return hipGetLastError();
 }
 
 template <int BQ, int BK, bool DENSE, typename OutT>
@@ -800,6 +716,17 @@ hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
 
 hipError_t launch_attention_dense(const AttnArgs& a, hipStream_t stream) {
   if (a.out_f32) return hipErrorInvalidValue;  // the maskless path writes bf16 only
+  // Without a mask the block size is only a tile size.  Where tiles of 64 would
+  // run unshared (parts_of), 128 x 128 tiles read half the K and V bytes per
+  // query and are faster (12 heads x 4000 tokens, d = 128: 133 -> 116 us); up
+  // to a few tiles of 64 the padding to 128 would cost more.
+  const int64_t items = (int64_t)a.B * a.H * a.n_qb;
+  if (a.blk_q == 64 && a.N >= 512 && parts_of((items + kXcds - 1) / kXcds, 4, a.n_kb) == 1) {
+    AttnArgs wide = a;
+    wide.blk_q = wide.blk_k = 128;
+    wide.n_qb = wide.n_kb = (a.N + 127) / 128;
+    return launch_any<true, __bf16>(wide, stream);
+  }
   return launch_any<true, __bf16>(a, stream);
 }
 

@@ -1,0 +1,96 @@
+"""Items shared by several slots of a workgroup (few items, many compute units) vs the reference."""
+
+import numpy as np
+import pytest
+
+import oracle
+from helpers import compare, to_bits
+from workloads import pack_rows
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # (B, H, N, d, blk_q, blk_k, p, seed): p = chance of a block
+    (1, 2, 1000, 128, 128, 128, 0.5, 1),    # two parts, ragged last block
+    (2, 1, 1030, 64, 128, 128, 0.3, 2),     # the last query and key block hold 6 tokens
+    (1, 3, 700, 128, 128, 64, 0.4, 3),
+    (1, 3, 700, 64, 128, 64, 0.4, 4),
+    (1, 2, 1000, 128, 64, 64, 0.5, 5),      # four parts
+    (2, 2, 577, 64, 64, 64, 0.2, 6),        # four parts, a last block of one token
+    (1, 2, 2050, 64, 64, 128, 0.3, 7),
+    (1, 2, 1100, 128, 64, 128, 0.3, 8),     # too large for LDS: never shared
+    (1, 8, 4096, 64, 128, 128, 0.05, 9),    # 256 items: the last shape with two parts
+    (1, 9, 3700, 64, 128, 128, 0.05, 10),   # 261 items: not shared
+    (1, 8, 2048, 64, 64, 64, 0.08, 11),     # 256 items of 64 rows: the last with four parts
+    (1, 9, 1850, 64, 64, 64, 0.08, 12),     # 261: two parts
+    (1, 16, 2048, 128, 64, 64, 0.05, 13),   # 512: the last with two parts
+    (1, 19, 1750, 64, 64, 64, 0.08, 14),    # 532: not shared
+    (1, 2, 480, 128, 64, 64, 0.5, 15),      # 8 key blocks: the shortest rows shared
+    (1, 2, 440, 128, 64, 64, 0.5, 16),      # 7: not shared
+]
+
+
+@pytest.mark.parametrize("B,H,N,d,blk_q,blk_k,p,seed", CASES)
+def test_shared_items_match_reference(B, H, N, d, blk_q, blk_k, p, seed):
+    import torch
+    from paper_2606_23019_amd import binding
+    rng = np.random.default_rng(seed)
+    n_qb, n_kb = -(-N // blk_q), -(-N // blk_k)
+    mask = rng.random((H, n_qb, n_kb)) < p
+    # rows of 0, 1, 2, 3 and 5 blocks: parts without a block; one row with all
+    for u, c in enumerate((0, 1, 2, 3, 5)):
+        mask[0, u % n_qb] = False
+        mask[0, u % n_qb, rng.choice(n_kb, c, replace=False)] = True
+    mask[-1, -1] = True
+    packed = pack_rows(mask)
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    q, k, v = (torch.randn((B, H, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    out, lse = binding.bsattn_fwd(q, k, v, packed, blk_q, blk_k)
+    ref = oracle.attention(to_bits(q), to_bits(k), to_bits(v), packed, blk_q, blk_k, d ** -0.5)
+    compare(out.float().cpu().numpy(), lse.cpu().numpy(), *ref)
+    # the same bits through the plan, in fp32 before rounding, on [B, N, H, d], and in any order
+    plan = binding.Plan(packed, B, H, N, blk_q, blk_k)
+    o2, l2 = plan(q, k, v)
+    o3, l3 = plan.fwd_f32out(q, k, v)
+    o4, l4 = binding.bsattn_fwd_bnhd(*(x.transpose(1, 2).contiguous() for x in (q, k, v)), packed,
+                                     blk_q, blk_k)
+    counts, lists = binding.mask_prepass(packed, H, n_qb, n_kb)
+    order = torch.from_numpy(rng.permutation(B * H * n_qb).astype(np.int32)).cuda()
+    o5, l5 = binding.bsattn_fwd_prepared(q, k, v, counts, lists, order, blk_q, blk_k)
+    for o, l in ((o2, l2), (o3.bfloat16(), l3), (o4.transpose(1, 2), l4), (o5, l5)):
+        assert torch.equal(o, out) and torch.equal(l, lse)
+
+
+@pytest.mark.parametrize("N,blk,d", [(1000, 128, 128), (1000, 64, 64)])
+def test_part_of_infinitely_low_logits_adds_nothing(N, blk, d):
+    # keys of the last blocks, a part of their own, have logits of -inf; the
+    # others are what is left
+    import torch
+    from paper_2606_23019_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q, k, v = (torch.randn((1, 1, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    q[..., 0] = q[..., 0].abs() + 1.0
+    n_kb = -(-N // blk)
+    kept = n_kb // 2
+    k[:, :, kept * blk:, 0] = -torch.inf
+    rows = np.ones((1, n_kb, n_kb), dtype=bool)
+    out, lse = binding.bsattn_fwd(q, k, v, pack_rows(rows), blk, blk)
+    rows[:, :, kept:] = False
+    kf = k.clone()
+    kf[:, :, kept * blk:] = 0.0
+    ref = oracle.attention(to_bits(q), to_bits(kf), to_bits(v), pack_rows(rows), blk, blk, d ** -0.5)
+    compare(out.float().cpu().numpy(), lse.cpu().numpy(), *ref)
+
+
+def test_wide_tiles_of_the_maskless_path_match_reference():
+    # blocks of 64 that would run unshared take 128 x 128 tiles from 512 tokens on
+    import torch
+    from paper_2606_23019_amd import binding
+    for (B, H, N, d) in ((2, 33, 515, 64), (1, 60, 640, 128), (1, 66, 511, 64)):
+        g = torch.Generator(device="cuda").manual_seed(N)
+        q, k, v = (torch.randn((B, H, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+        out, lse = binding.dense_attn_fwd(q, k, v, 64)
+        n = -(-N // 64)
+        ones = pack_rows(np.ones((H, n, n), dtype=bool))
+        ref = oracle.attention(to_bits(q), to_bits(k), to_bits(v), ones, 64, 64, d ** -0.5)
+        compare(out.float().cpu().numpy(), lse.cpu().numpy(), *ref)

@@ -1,0 +1,52 @@
+"""The static checks of test_kernel_isa on the kernels whose items are shared by several slots."""
+
+import re
+from collections import Counter
+
+from test_kernel_isa import HIPCC, SRC, ROOT
+
+import os
+import subprocess
+
+import pytest
+
+
+@pytest.fixture(scope="module")
+def split_kernels(tmp_path_factory):
+    if not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    from paper_2606_23019_amd import build
+    out = str(tmp_path_factory.mktemp("isa") / "attn.s")
+    subprocess.run([HIPCC] + [f for f in build.HIPCC_FLAGS if f not in ("-shared", "-fPIC")] + [
+        "-I", os.path.join(ROOT, "include"), "-I", os.path.dirname(SRC), "--cuda-device-only", "-S",
+        "-o", out, SRC], check=True, capture_output=True)
+    text = open(out).read()
+    names = sorted(set(re.findall(r"^(_ZN2sa\S+bsattn_split_kernel\S+):", text, re.M)))
+    code = {n: text[text.index("\n%s:" % n):] for n in names}
+    code = {n: c[:c.index(".Lfunc_end")].split("\n") for n, c in code.items()}
+    meta = {re.search(r"\.name:\s+(\S+)", b).group(1): b
+            for b in text.split("  - .agpr_count")[1:] if ".name:" in b}
+    return code, meta
+
+
+def test_split_kernels_found(split_kernels):
+    code, _ = split_kernels
+    # 128-row items in two parts: two key block sizes x two head dims, bf16 or fp32 out, and the
+    # square ones maskless; 64-row items in two and four: (64, 64) x two head dims and (64, 128)
+    # with d = 64, bf16 or fp32 out, and the square ones maskless
+    assert len(code) == (4 * 2 + 2) + 2 * (3 * 2 + 2), sorted(code)
+
+
+def test_split_kernels_keep_no_scratch_and_only_copies_in_loops(split_kernels):
+    code, meta = split_kernels
+    for name, lines in code.items():
+        for key in ("vgpr_spill_count", "private_segment_fixed_size"):
+            assert int(re.search(r"\.%s:\s+(\d+)" % key, meta[name]).group(1)) == 0, (name, key)
+        marked = [i for i, l in enumerate(lines) if "in Loop:" in l or "Loop Header" in l]
+        assert marked, name
+        hi = max(marked) + 1
+        while hi < len(lines) and not re.match(r"^\.LBB", lines[hi]):
+            hi += 1
+        ops = Counter(l.split()[0] for l in lines[min(marked):hi]
+                      if re.match(r"^\s+(global_|buffer_|scratch_|flat_)", l))
+        assert set(ops) == {"global_load_lds_dwordx4"}, (name, dict(ops))
