@@ -614,7 +614,8 @@ constexpr bool kReadAhead = BQ == 128 && (DENSE || PARTS > 1);
   const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K, const __bf16 *__restrict__ V,       \
       const int32_t *__restrict__ counts, const int32_t *__restrict__ lists,                      \
       const int32_t *__restrict__ order, OutT *__restrict__ O, float *__restrict__ LSE, int H,    \
-      int N, int n_qb, int n_kb, float c_log2, int64_t sb, int64_t sh, int sn, int n_items
+      int N, int n_qb, int n_kb, float c_log2, int64_t sb, int64_t sh, int sn, int n_items,           \
+      int place0
 
 template <int BQ, int BK, int D, bool DENSE, typename OutT>
 __global__ __launch_bounds__(512, 1) void bsattn_fwd_pp_kernel(SA_PP_PARAMS) {
@@ -651,16 +652,33 @@ inline int parts_of(int64_t seq, int slots, int n_kb) {
   return parts;
 }
 
+// Places at the end of every XCD's sequence whose maskless items are shared by
+// two slots, in a launch of their own.  All items are of one length, so a
+// sequence runs in rounds of kCus workgroups of two items, and a last round of
+// up to kCus items leaves half of the compute units or more idle for as long as
+// a full one takes; shared, it takes half as long (a fuller one would need two
+// such rounds).  Measured start -> shared, us: d = 128, 5 heads x 32760 tokens
+// (2.5 rounds) 2572 -> 2426, 5 x 14000 (1.1) 708 -> 577, 2 x 20 x 2000 (1.25)
+// 118 -> 104, 40 x 1024 in batches of 2 (1.25, 8 key blocks) 72 -> 68, 20 x
+// 33800 (10.4) 10827 -> 10582, 40 x 20000 (12.3) 7649 -> 7527; d = 64, 2 x 20 x
+// 2000 81 -> 68.  Masked items differ in length, and those at the end of the
+// order are the lightest: there the last round is short already.
+inline int64_t shared_rest(int64_t seq, int n_kb) {
+  const int64_t rest = seq % (2 * kCus);
+  return n_kb >= 8 && seq > 2 * kCus && rest <= kCus ? rest : 0;
+}
+
 template <int BQ, int BK, int D, bool DENSE, typename OutT, int PARTS>
-hipError_t launch_pp(const AttnArgs& a, int64_t n_items, int64_t seq, hipStream_t stream) {
-  // consecutive items of one XCD's sequence per workgroup
+hipError_t launch_pp(const AttnArgs& a, int64_t n_items, int64_t place0, int64_t end,
+                     hipStream_t stream) {
+  // consecutive items of one XCD's sequence per workgroup, places place0 .. end - 1
   constexpr int kItems = PingPong<BQ, BK, D>::kItems / PARTS;
-  const int64_t n_wg = kXcds * ((seq + kItems - 1) / kItems);
+  const int64_t n_wg = kXcds * ((end - place0 + kItems - 1) / kItems);
   auto args = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(512), 0, stream, (const __bf16*)a.q,
                        (const __bf16*)a.k, (const __bf16*)a.v, a.counts, a.lists, a.order,
                        (OutT*)a.out, a.lse, a.H, a.N, a.n_qb, a.n_kb, a.scale * kLog2e, a.sb, a.sh,
-                       a.sn, (int)n_items);
+                       a.sn, (int)n_items, (int)place0);
   };
   if constexpr (PARTS == 1)
     args(bsattn_fwd_pp_kernel<BQ, BK, D, DENSE, OutT>);
@@ -677,11 +695,19 @@ hipError_t launch_tile(const AttnArgs& a, hipStream_t stream) {
     constexpr int kSlots = PingPong<BQ, BK, D>::kItems;
     const int parts = parts_of(seq, kSlots, a.n_kb);
     if constexpr (kSlots == 4)
-      if (parts == 4) return launch_pp<BQ, BK, D, DENSE, OutT, 4>(a, n_items, seq, stream);
-    if (parts == 2) return launch_pp<BQ, BK, D, DENSE, OutT, 2>(a, n_items, seq, stream);
+      if (parts == 4) return launch_pp<BQ, BK, D, DENSE, OutT, 4>(a, n_items, 0, seq, stream);
+    if (parts == 2) return launch_pp<BQ, BK, D, DENSE, OutT, 2>(a, n_items, 0, seq, stream);
   }
   if constexpr (kUsePingPong<BQ, BK, D, DENSE>) {
-    return launch_pp<BQ, BK, D, DENSE, OutT, 1>(a, n_items, seq, stream);
+    if constexpr (DENSE && BQ == 128 && BK == 128) {
+      const int64_t rest = shared_rest(seq, a.n_kb);
+      if (rest > 0) {
+        const hipError_t e = launch_pp<BQ, BK, D, DENSE, OutT, 1>(a, n_items, 0, seq - rest, stream);
+        if (e != hipSuccess) return e;
+        return launch_pp<BQ, BK, D, DENSE, OutT, 2>(a, n_items, seq - rest, seq, stream);
+      }
+    }
+    return launch_pp<BQ, BK, D, DENSE, OutT, 1>(a, n_items, 0, seq, stream);
   } else {
     hipLaunchKernelGGL((bsattn_fwd_kernel<BQ, BK, D, DENSE, OutT>), dim3((unsigned)n_items),
                        dim3(Tile<BQ, BK, D>::kThreads), 0, stream, (const __bf16*)a.q,

@@ -20,9 +20,12 @@
   __bf16* Vs = Vs_all[slot];
 
   // Workgroup b on XCD b mod 8 takes items kItems (b / 8) .. + kItems - 1 of
-  // that XCD's sequence: the launch positions x + 8 j of the one-item layout.
+  // that XCD's sequence: the launch positions x + 8 j of the one-item layout
+  // (maskless: from place0 on).
+  const int from = DENSE ? place0 : 0;
   auto pos_of = [&](int sl) -> int64_t {
-    return (int64_t)(blockIdx.x % kXcds) + kXcds * (kItems * (int64_t)(blockIdx.x / kXcds) + sl);
+    return (int64_t)(blockIdx.x % kXcds) +
+           kXcds * (from + kItems * (int64_t)(blockIdx.x / kXcds) + sl);
   };
   // The look-ups are branch-free (positions clamped, validity applied after
   // the loads), so that the scalar loads of all items go out together:

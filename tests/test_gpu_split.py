@@ -94,3 +94,22 @@ def test_wide_tiles_of_the_maskless_path_match_reference():
         ones = pack_rows(np.ones((H, n, n), dtype=bool))
         ref = oracle.attention(to_bits(q), to_bits(k), to_bits(v), ones, 64, 64, d ** -0.5)
         compare(out.float().cpu().numpy(), lse.cpu().numpy(), *ref)
+
+
+@pytest.mark.parametrize("B,H,N,d,blk", [
+    (1, 57, 1100, 64, 128),    # 513 items, 65 places an XCD: one round and one shared place
+    (1, 57, 1030, 128, 64),    # the same by way of 128 x 128 tiles, ragged
+    (2, 48, 1024, 64, 128),    # 96 places: the longest shared rest
+    (1, 97, 961, 64, 128),     # 97: not shared
+    (1, 74, 896, 64, 128),     # 65 places, rows of 7 key blocks: not shared
+])
+def test_shared_last_round_of_the_maskless_path(B, H, N, d, blk):
+    import torch
+    from paper_2606_23019_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn((B, H, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    out, lse = binding.dense_attn_fwd(q, k, v, blk)
+    n = -(-N // 128)
+    ones = pack_rows(np.ones((H, n, n), dtype=bool))
+    ref = oracle.attention(to_bits(q), to_bits(k), to_bits(v), ones, 128, 128, d ** -0.5)
+    compare(out.float().cpu().numpy(), lse.cpu().numpy(), *ref)
