@@ -67,7 +67,9 @@ SA_API int sa_version(void);
  * One-shot forward pass (Sec. 4.3.2): runs the mask pre-pass, the schedule
  * and the attention kernel on `stream`.  Internal workspace (per-row counts
  * and key-block lists, the work order) is taken with stream-ordered
- * hipMallocAsync and released with hipFreeAsync on the same stream.
+ * hipMallocAsync and released with hipFreeAsync on the same stream.  Shapes
+ * whose query blocks all run at once (up to 256 of them over the heads, 8 or
+ * more key blocks) need neither: their attention kernel reads the mask itself.
  * Returns SA_OK, SA_ERR_INVALID_ARG, SA_ERR_UNSUPPORTED or SA_ERR_HIP.
  */
 SA_API int sa_bsattn_fwd(const void* q, const void* k, const void* v,

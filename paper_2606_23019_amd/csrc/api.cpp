@@ -229,18 +229,27 @@ static int check_oneshot(const void* q, const void* k, const void* v, const uint
 }
 
 // Pre-pass, schedule and attention of a checked one-shot call, with the
-// workspace laid out by plan_workspace at ws.
+// workspace laid out by plan_workspace at ws; without ws (only where
+// attention_reads_mask) the attention kernel alone, on the mask itself.
 static hipError_t launch_oneshot(const void* q, const void* k, const void* v,
                                  const uint64_t* mask_bits, void* out, float* lse, int B, int H,
                                  int N, int d, int blk_q, int blk_k, float scale, int layout,
                                  bool out_f32, const Dims& dm, void* ws, hipStream_t s) {
+  const bool bnhd = layout == SA_LAYOUT_BNHD;
+  const int sn = bnhd ? H * d : d;
+  if (!ws) {
+    sa::AttnArgs a{q, k, v, nullptr, nullptr, nullptr, out, lse, B, H, N, d, blk_q, blk_k,
+                   dm.n_qb, dm.n_kb, scale,
+                   (int64_t)H * N * d, bnhd ? (int64_t)d : (int64_t)N * d, sn};
+    a.out_f32 = out_f32;
+    a.mask_bits = mask_bits;
+    return sa::launch_attention(a, s);
+  }
   const Workspace w = plan_workspace(B, H, dm);
   char* base = (char*)ws;
   int32_t* counts = (int32_t*)(base + w.counts_off);
   int32_t* lists = (int32_t*)(base + w.lists_off);
   int32_t* order = (int32_t*)(base + w.order_off);
-  const bool bnhd = layout == SA_LAYOUT_BNHD;
-  const int sn = bnhd ? H * d : d;
   hipError_t e = sa::launch_prepass(mask_bits, H, dm.n_qb, dm.n_kb, counts, lists, s);
   if (e == hipSuccess) e = sa::launch_schedule(counts, B, H, dm.n_qb, order, s);
   if (e == hipSuccess) {
@@ -262,6 +271,9 @@ static int fwd_oneshot(const void* q, const void* k, const void* v, const uint64
                                layout, out_f32, &dm);
   if (st != SA_OK) return st;
   hipStream_t s = (hipStream_t)stream;
+  if (sa::attention_reads_mask(B, H, dm.n_qb, dm.n_kb, d, blk_q, blk_k))
+    return launch_oneshot(q, k, v, mask_bits, out, lse, B, H, N, d, blk_q, blk_k, scale, layout,
+                          out_f32, dm, nullptr, s) == hipSuccess ? SA_OK : SA_ERR_HIP;
   const Workspace w = plan_workspace(B, H, dm);
   void* ws = nullptr;
   if (hipMallocAsync(&ws, w.total, s) != hipSuccess || !ws) return SA_ERR_HIP;
@@ -314,8 +326,10 @@ SA_API int sa_bsattn_fwd_noalloc(const void* q, const void* k, const void* v,
   if (st != SA_OK) return st;
   if (plan_workspace(B, H, dm).total > (size_t)SA_NOALLOC_SCRATCH_BYTES) return SA_ERR_TOO_LARGE;
   void* ws = nullptr;
-  st = scratch_on_current_device(&ws);
-  if (st != SA_OK) return st;
+  if (!sa::attention_reads_mask(B, H, dm.n_qb, dm.n_kb, d, blk_q, blk_k)) {
+    st = scratch_on_current_device(&ws);
+    if (st != SA_OK) return st;
+  }
   // Nothing in the scratch has to start at zero: the pre-pass writes every
   // count and every list entry up to the count, the schedule every order entry.
   const hipError_t e = launch_oneshot(q, k, v, mask_bits, out, lse, B, H, N, d, blk_q, blk_k,

@@ -610,21 +610,38 @@ constexpr bool kReadAhead = BQ == 128 && (DENSE || PARTS > 1);
 // places, see parts_of().  The two kernels have one body, included as text: as
 // an inlined function it was scheduled otherwise (V operands read only when
 // they are needed) and ran up to 5 % slower.
+constexpr int kMaskWords = 8;  // words of a mask row that the kernel walks itself: 256 items a head at most, 128 x 64 blocks
 #define SA_PP_PARAMS                                                                              \
   const __bf16 *__restrict__ Q, const __bf16 *__restrict__ K, const __bf16 *__restrict__ V,       \
       const int32_t *__restrict__ counts, const int32_t *__restrict__ lists,                      \
       const int32_t *__restrict__ order, OutT *__restrict__ O, float *__restrict__ LSE, int H,    \
       int N, int n_qb, int n_kb, float c_log2, int64_t sb, int64_t sh, int sn, int n_items,           \
-      int place0
+      int place0, const uint64_t *__restrict__ mask
 
 template <int BQ, int BK, int D, bool DENSE, typename OutT>
 __global__ __launch_bounds__(512, 1) void bsattn_fwd_pp_kernel(SA_PP_PARAMS) {
   constexpr int PARTS = 1;
+  constexpr bool FROM_MASK = false;
 #include "attn_pp_body.h"
 }
 
 template <int BQ, int BK, int D, bool DENSE, typename OutT, int PARTS>
 __global__ __launch_bounds__(512, 1) void bsattn_split_kernel(SA_PP_PARAMS) {
+  constexpr bool FROM_MASK = false;
+#include "attn_pp_body.h"
+}
+
+// One item a workgroup, its key blocks read off the mask row's words by a
+// bit scan (a count of trailing zeros, the lowest bit cleared), which stays in
+// scalar registers and takes the place of the list.  With every item on the
+// chip at once an order has nothing to give either, so a one-shot call of such
+// a shape is this one launch, with no pre-pass, schedule or workspace.
+// Those three took longer than the attention: 1 x 1024 tokens, d = 64, blocks
+// of 64 49.7 -> 19.0 us a call.
+template <int BQ, int BK, int D, typename OutT, int PARTS>
+__global__ __launch_bounds__(512, 1) void bsattn_mask_split_kernel(SA_PP_PARAMS) {
+  constexpr bool DENSE = false;
+  constexpr bool FROM_MASK = true;
 #include "attn_pp_body.h"
 }
 #undef SA_PP_PARAMS
@@ -678,8 +695,13 @@ hipError_t launch_pp(const AttnArgs& a, int64_t n_items, int64_t place0, int64_t
     hipLaunchKernelGGL(kernel, dim3((unsigned)n_wg), dim3(512), 0, stream, (const __bf16*)a.q,
                        (const __bf16*)a.k, (const __bf16*)a.v, a.counts, a.lists, a.order,
                        (OutT*)a.out, a.lse, a.H, a.N, a.n_qb, a.n_kb, a.scale * kLog2e, a.sb, a.sh,
-                       a.sn, (int)n_items, (int)place0);
+                       a.sn, (int)n_items, (int)place0, a.mask_bits);
   };
+  if constexpr (kItems == 1 && !DENSE)
+    if (a.mask_bits) {
+      args(bsattn_mask_split_kernel<BQ, BK, D, OutT, PARTS>);
+      return hipGetLastError();
+    }
   if constexpr (PARTS == 1)
     args(bsattn_fwd_pp_kernel<BQ, BK, D, DENSE, OutT>);
   else
@@ -736,7 +758,16 @@ hipError_t launch_any(const AttnArgs& a, hipStream_t stream) {
 
 }  // namespace
 
+bool attention_reads_mask(int B, int H, int n_qb, int n_kb, int d, int blk_q, int blk_k) {
+  const int slots = blk_q == 128 ? 2 : 4;
+  if (slots * 4 * blk_k * d > 160 * 1024) return false;  // PingPong::kFits
+  const int64_t seq = ((int64_t)B * H * n_qb + kXcds - 1) / kXcds;
+  return n_kb <= 64 * kMaskWords && parts_of(seq, slots, n_kb) == slots;
+}
+
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream) {
+  if (a.mask_bits && !attention_reads_mask(a.B, a.H, a.n_qb, a.n_kb, a.d, a.blk_q, a.blk_k))
+    return hipErrorInvalidValue;
   return a.out_f32 ? launch_any<false, float>(a, stream) : launch_any<false, __bf16>(a, stream);
 }
 

@@ -1,5 +1,6 @@
 // Body of the ping-pong kernels (attn_fwd.hip, where it is described), included in
-// bsattn_fwd_pp_kernel and bsattn_split_kernel; not a header of its own.
+// bsattn_fwd_pp_kernel, bsattn_split_kernel and bsattn_mask_split_kernel; not a
+// header of its own.
   using T = Tile<BQ, BK, D>;
   constexpr int kSlots = PingPong<BQ, BK, D>::kItems;  // places for an item in a workgroup
   constexpr int kItems = kSlots / PARTS;               // items per workgroup
@@ -35,7 +36,7 @@
 #pragma unroll
   for (int sl = 0; sl < kItems; ++sl) {
     const int64_t pos = min(pos_of(sl), (int64_t)n_items - 1);
-    if (DENSE) {
+    if (DENSE || FROM_MASK) {
       int uu;
       const int unit = xcd_slice(pos, n_items / n_qb, n_qb, &uu);
       it_of[sl] = min(max(unit * n_qb + uu, 0), n_items - 1);
@@ -49,17 +50,47 @@
 #pragma unroll
   for (int sl = 0; sl < kItems; ++sl) {
     const int it = min(max(it_of[sl], 0), n_items - 1);
-    c_of[sl] = DENSE ? n_kb : counts[(it / n_qb) % H * n_qb + it % n_qb];
+    c_of[sl] = DENSE || FROM_MASK ? n_kb : counts[(it / n_qb) % H * n_qb + it % n_qb];
     if (sl == mine) item = it;
   }
   const int bh = item / n_qb;
   const int u = item - bh * n_qb;
   const int h = bh % H;
   const int row = h * n_qb + u;
-  const int32_t* list = DENSE ? nullptr : lists + (int64_t)row * n_kb;
+  const int32_t* list = DENSE || FROM_MASK ? nullptr : lists + (int64_t)row * n_kb;
+  // FROM_MASK: the row's words (by scalar loads: vector ones would wait for the tile
+  // copies), the walk's current one, and its blocks not yet taken
+  const int words = (n_kb + 63) / 64;
+  using MaskWord = const __attribute__((address_space(4))) uint64_t;
+  MaskWord* mrow = FROM_MASK ? (MaskWord*)(uintptr_t)(mask + (int64_t)row * words) : nullptr;
+  auto word_at = [&](int w) {
+    const int real = n_kb - 64 * w;  // bits of the word that name a key block, >= 1
+    return mrow[w] & (real < 64 ? (1ull << real) - 1ull : ~0ull);
+  };
+  int w_cur = 0;
+  uint64_t left = 0;
+  if constexpr (FROM_MASK) {
+    static_assert(kItems == 1, "one row a workgroup");
+    // all words requested before the first is counted; past the row's end its
+    // last word, which does not count
+    uint64_t word[kMaskWords];
+#pragma unroll
+    for (int w = 0; w < kMaskWords; ++w) word[w] = word_at(min(w, words - 1));
+    c_of[0] = 0;
+#pragma unroll
+    for (int w = 0; w < kMaskWords; ++w) c_of[0] += w < words ? __popcll(word[w]) : 0;
+    left = word[0];
+  }
+  // takes the row's next block; there has to be one
+  auto next_block = [&]() {
+    while (left == 0 && w_cur + 1 < words) left = word_at(++w_cur);
+    const int bit = left ? __builtin_ctzll(left) : 0;
+    left &= left - 1;
+    return 64 * w_cur + bit;
+  };
   int t0 = 0;  // place of this group's first key block (maskless)
   auto kblk = [&](int t) { return DENSE ? t0 + t : min(max(list[t], 0), n_kb - 1); };
-  int first = kblk(0);  // in range for every row (n_kb >= 1): read before cnt is known
+  int first = FROM_MASK ? 0 : kblk(0);  // in range for every row (n_kb >= 1): read before cnt is known
   asm volatile("" : "+s"(first));     // keeps that load here, not inside the cnt > 0 branch
   __builtin_amdgcn_sched_barrier(0);  // counts and the first key block issued together
   // every item's count: all groups run max(counts) iterations
@@ -75,9 +106,28 @@
     const int run = (cnt + PARTS - 1) / PARTS;
     t0 = min(part * run, cnt);
     cnt = min(run, cnt - t0);
-    if (!DENSE) list += t0;
-    if (cnt > 0) first = kblk(0);
+    if constexpr (FROM_MASK) {
+      if (cnt > 0) {
+        // to block t0: past the words wholly before it, then past the bits
+        int skip = t0;
+        for (; w_cur + 1 < words; left = word_at(++w_cur)) {
+          const int n = __popcll(left);
+          if (skip < n) break;
+          skip -= n;
+        }
+        int bit = 0;  // of the word's block of rank skip
+#pragma unroll
+        for (int step = 32; step > 0; step /= 2)
+          if (__popcll(left & ((1ull << (bit + step)) - 1ull)) <= skip) bit += step;
+        left &= ~0ull << bit;
+        first = next_block();
+      }
+    } else {
+      if (!DENSE) list += t0;
+      if (cnt > 0) first = kblk(0);
+    }
   }
+  int now = first;  // FROM_MASK: the block whose K tile was requested last
   const bool has_item = pos_of(mine) < n_items;
 
   const int64_t base = (int64_t)(bh / H) * sb + (int64_t)h * sh;
@@ -193,7 +243,7 @@
 
     // ---- softmax phase of block t; copies of V[t] and K[t + 1]
     if (do_s) {
-      const int key0 = kblk(t) * BK;
+      const int key0 = (FROM_MASK ? now : kblk(t)) * BK;
       const bool more = t + 1 < cnt;
       issue_tile_copy<T, BK, D>(Vs, Vb, key0, N, sn, gwave_u, lane, cp);
       if (key0 + BK > N) {
@@ -211,7 +261,10 @@
 #pragma unroll
         for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kg][i]);
       mx = pair_max(mx) * c_log2;
-      if (more) issue_tile_copy<T, BK, D>(Ks, Kb, kblk(t + 1) * BK, N, sn, gwave_u, lane, cp);
+      if (more) {
+        if (FROM_MASK) now = next_block();
+        issue_tile_copy<T, BK, D>(Ks, Kb, (FROM_MASK ? now : kblk(t + 1)) * BK, N, sn, gwave_u, lane, cp);
+      }
       const bool grow = mx > m_run;
       if (__any(grow)) {
         const float m_new = grow ? mx : m_run;

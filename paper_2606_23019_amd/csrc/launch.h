@@ -25,6 +25,8 @@ struct AttnArgs {
   int64_t sb, sh;
   int sn;
   bool out_f32 = false;  // out is fp32 instead of bf16 (masked path only)
+  // mask rows, in place of counts, lists and order, where attention_reads_mask()
+  const uint64_t* mask_bits = nullptr;
 };
 
 hipError_t launch_prepass(const uint64_t* mask_bits, int H, int n_qb, int n_kb, int32_t* counts,
@@ -47,6 +49,9 @@ bool fidelity_supported(int R, int K);
 hipError_t launch_fidelity(const void* q, const void* k, const int32_t* rows, int R, const float* T,
                            const float* p, int K, float* blk_lse, float* hel, float* fid, int B,
                            int H, int N, int d, int blk, float scale, hipStream_t stream);
+
+// Whether the attention kernel of this shape can walk the mask rows itself.
+bool attention_reads_mask(int B, int H, int n_qb, int n_kb, int d, int blk_q, int blk_k);
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t stream);
 

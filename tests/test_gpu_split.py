@@ -113,3 +113,40 @@ def test_shared_last_round_of_the_maskless_path(B, H, N, d, blk):
     ones = pack_rows(np.ones((H, n, n), dtype=bool))
     ref = oracle.attention(to_bits(q), to_bits(k), to_bits(v), ones, 128, 128, d ** -0.5)
     compare(out.float().cpu().numpy(), lse.cpu().numpy(), *ref)
+
+
+@pytest.mark.parametrize("H,N,d,blk_q,blk_k,p", [
+    (1, 16400, 64, 128, 64, 0.03),    # rows of 5 words, the last of one block
+    (1, 32768, 128, 128, 64, 0.02),   # 8 full words: the longest rows walked off the mask
+    (1, 32768, 64, 128, 128, 0.01),   # 4 words, many of them empty
+    (1, 8250, 128, 64, 64, 0.3),      # four parts, 3 words
+    (1, 16384, 64, 64, 128, 0.05),    # four parts, 2 words
+    (3, 4100, 128, 128, 128, 0.5),
+])
+def test_walk_off_the_mask_gives_the_bits_of_the_list(H, N, d, blk_q, blk_k, p):
+    # one-shot calls of these shapes scan the mask rows in the attention kernel; a plan
+    # walks the pre-pass's lists.  Bits past the last key block do not count.
+    import torch
+    from paper_2606_23019_amd import binding
+    rng = np.random.default_rng(N + d)
+    n_qb, n_kb = -(-N // blk_q), -(-N // blk_k)
+    mask = rng.random((H, n_qb, n_kb)) < p
+    for u, at in enumerate(([], [0], [n_kb - 1], [0, n_kb - 1], [n_kb // 2], list(range(n_kb)))):
+        mask[0, u] = False
+        mask[0, u, at] = True
+    mask[0, 6] = np.arange(n_kb) >= n_kb // 2
+    packed = pack_rows(mask)
+    noisy = packed.copy()
+    if n_kb % 64:
+        noisy[..., -1] |= np.uint64((2 ** 64 - 1) ^ (2 ** (n_kb % 64) - 1))
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn((1, H, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    plan = binding.Plan(packed, 1, H, N, blk_q, blk_k)
+    want, want_lse = plan.fwd_f32out(q, k, v)
+    out, lse = binding.bsattn_fwd_f32out(q, k, v, noisy, blk_q, blk_k)
+    assert torch.equal(out, want) and torch.equal(lse, want_lse)
+    out, lse = binding.bsattn_fwd(q, k, v, noisy, blk_q, blk_k)
+    assert torch.equal(out, plan(q, k, v)[0]) and torch.equal(lse, want_lse)
+    t = [x.transpose(1, 2).contiguous() for x in (q, k, v)]
+    out, lse = binding.bsattn_fwd_bnhd(*t, noisy, blk_q, blk_k)
+    assert torch.equal(out.transpose(1, 2), plan(q, k, v)[0]) and torch.equal(lse, want_lse)
