@@ -145,8 +145,8 @@ constexpr int kFidMaxK = 64;
 // blocks.  Latency bounds it: with a wavefront's 64 lanes all walking every
 // block and taking its exponential, and the mean in a launch of its own, it
 // took 15.9 us and a launch, 10.4 now (40 heads, 16 rows, 16 candidates, 256
-// blocks; the whole call 89.6 -> 79.4 us).  At the end
-// the rows of the head give its Fidelity Score, 1 - their mean.
+// blocks; the whole call 89.6 -> 79.4 us).  At the end the rows of the head
+// give its Fidelity Score, 1 - their mean.
 constexpr int kRowWaves = 16;
 constexpr int kRowChunk = 256;
 
