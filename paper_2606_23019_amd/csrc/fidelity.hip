@@ -20,7 +20,9 @@
 // Kernel 2 (one workgroup per head, one wavefront per sampled row): the row's
 // dense log-normaliser from its block log-masses, then for each candidate p
 // the dropped mass over blocks with !(T <= p) and H from the closed form above,
-// and 1 - H averaged over the head's rows, the Fidelity Score (Eq. 4).
+// and 1 - H averaged over the head's rows, the Fidelity Score (Eq. 4).  With
+// more than 16 candidates the rows are spread over the chip and the average is
+// a kernel of its own.
 
 #include <math.h>
 
@@ -223,6 +225,59 @@ __global__ __launch_bounds__(64 * kRowWaves) void fid_row_kernel(
   }
 }
 
+// One wavefront per sampled row (b, h, i); lane c owns candidate c (K <= 64).
+// The row's dense log-normaliser comes from its block log-masses (lanes over
+// blocks), then every lane walks all blocks: the block's mass and map entry
+// are the same for the whole wavefront, and lane c adds the mass when the
+// block is off for its threshold.  Each block costs a few instructions
+// whatever the number of candidates, and no per-candidate reduction is left.
+__global__ __launch_bounds__(64 * kFidWaves) void fid_row_wide_kernel(
+    const float* __restrict__ blk_lse, const int32_t* __restrict__ rows, int R,
+    const float* __restrict__ T, const float* __restrict__ p, int K, int H, int N, int blk,
+    int n_qb, int n_kb, float* __restrict__ hel) {
+  const int lane = threadIdx.x & 63;
+  const int i = blockIdx.y * kFidWaves + (threadIdx.x >> 6);
+  if (i >= R) return;  // uniform per wavefront
+  const int bh = blockIdx.x;
+  const int h = bh % H;
+  const float* lrow = blk_lse + ((int64_t)bh * R + i) * n_kb;
+  const int r = min(max(rows[(int64_t)h * R + i], 0), N - 1);
+  const float* trow = T + ((int64_t)h * n_qb + r / blk) * n_kb;
+  float mx = -INFINITY;
+  for (int v = lane; v < n_kb; v += 64) mx = fmaxf(mx, lrow[v]);
+  mx = wave_max(mx);
+  float z = 0.f;
+  for (int v = lane; v < n_kb; v += 64) z += __expf(lrow[v] - mx);
+  const float lse = mx + __logf(wave_sum(z));
+  const float pc = lane < K ? p[lane] : 0.f;
+  float dropped = 0.f;
+  bool kept = false;
+#pragma unroll 8
+  for (int v = 0; v < n_kb; ++v) {
+    const float t = trow[v];                 // wavefront-uniform address
+    const float mass = __expf(lrow[v] - lse);
+    if (t <= pc)                             // NaN on either side: block off
+      kept = true;
+    else
+      dropped += mass;
+  }
+  dropped = fminf(fmaxf(dropped, 0.f), 1.f);
+  if (lane < K)
+    hel[((int64_t)bh * R + i) * K + lane] = kept ? sqrtf(dropped / (1.f + sqrtf(1.f - dropped))) : 1.f;
+}
+
+// Fidelity Score per (b, h, candidate): 1 - mean over the sampled rows.
+__global__ __launch_bounds__(256) void fid_mean_kernel(const float* __restrict__ hel, int R, int K,
+                                                       int64_t n_out, float* __restrict__ fid) {
+  const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;  // o = bh * K + c
+  if (o >= n_out) return;
+  const int64_t bh = o / K;
+  const int c = (int)(o - bh * K);
+  float acc = 0.f;
+  for (int i = 0; i < R; ++i) acc += hel[(bh * R + i) * K + c];
+  fid[o] = 1.f - acc / (float)R;
+}
+
 }  // namespace
 
 bool fidelity_supported(int R, int K) { return R >= 1 && R <= kFidMaxR && K >= 1 && K <= kFidMaxK; }
@@ -243,10 +298,26 @@ hipError_t launch_fidelity(const void* q, const void* k, const int32_t* rows, in
                        (const __bf16*)q, (const __bf16*)k, rows, R, H, N, blk, n_kb, c_log2, blk_lse);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
+  // With many candidates few groups of lanes are left to share a row's blocks,
+  // and a head's rows on one compute unit wait for its LDS: 40 heads x 75600
+  // tokens, 32 rows, 64 candidates took 228 us a call that way and 211 with a
+  // wavefront of its own for each row over the chip; 5 x 75600, 16 rows, 8
+  // candidates 43 and 68, 40 x 32760, 16 and 16, 79 and 90.
   int span = 1;
   while (span < K) span *= 2;
-  hipLaunchKernelGGL(fid_row_kernel, dim3(B * H), dim3(64 * kRowWaves), 0, stream, blk_lse, rows, R,
-                     T, p, K, span, H, N, blk, n_qb, n_kb, hel, fid);
+  if (span <= 16) {
+    hipLaunchKernelGGL(fid_row_kernel, dim3(B * H), dim3(64 * kRowWaves), 0, stream, blk_lse, rows, R,
+                       T, p, K, span, H, N, blk, n_qb, n_kb, hel, fid);
+    return hipGetLastError();
+  }
+  hipLaunchKernelGGL(fid_row_wide_kernel, dim3(B * H, (R + kFidWaves - 1) / kFidWaves),
+                     dim3(64 * kFidWaves), 0, stream, blk_lse, rows, R, T, p, K, H, N, blk, n_qb,
+                     n_kb, hel);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const int64_t n_out = (int64_t)B * H * K;
+  hipLaunchKernelGGL(fid_mean_kernel, dim3((unsigned)((n_out + 255) / 256)), dim3(256), 0, stream,
+                     hel, R, K, n_out, fid);
   return hipGetLastError();
 }
 
