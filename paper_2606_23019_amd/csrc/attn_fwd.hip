@@ -494,6 +494,17 @@ struct PingPong {
 template <int BQ, int BK, int D, bool DENSE>
 constexpr bool kUsePingPong = PingPong<BQ, BK, D>::kFits && (BQ == 128 || DENSE);
 
+// What stands for a maximum of -inf in the exponents of part `part`.  A walk
+// over all blocks has a finite maximum when it comes to a block whose logits
+// are all -inf, and gives it weights of 0, unless that is its first block,
+// whose weights exp2(-inf + inf) are NaN.  So a first part keeps -inf, and the
+// later ones, whose walk may begin with such a block, take the lowest finite
+// value instead: -inf weighs 0, and NaN stays NaN.
+template <int PARTS>
+__device__ __forceinline__ float part_floor(int part) {
+  return PARTS > 1 && part > 0 ? -3.402823466e+38f : -INFINITY;
+}
+
 // Puts together the PARTS parts of the workgroup's shared items: maxima, sums
 // and accumulators of parts 1 .. go through LDS into those of part 0, which
 // end up as the item's.  Every wavefront of the workgroup calls this, when the
@@ -540,14 +551,15 @@ __device__ __forceinline__ void merge_parts(f32x16 (&o)[D / 32], float& m, float
       lp[p] = stats(p)[1];
       m = fmaxf(m, mp[p]);
     }
-    // A part whose maximum is -inf (no key blocks, or nothing but logits of
-    // -inf) adds nothing to one that has a finite one: its sums may be NaN.
+    // A part of no key blocks, or of logits that are all -inf, has m = -inf and
+    // sums of 0 (see part_floor): a weight of exp2(-inf) = 0 adds nothing.  A
+    // part of NaN logits has m = -inf too and sums of NaN, which every weight
+    // keeps, as the walk over all blocks in one would.
     l = 0.f;
 #pragma unroll
     for (int p = 0; p < PARTS; ++p) {
-      const bool none = mp[p] == -INFINITY && m != -INFINITY;
-      scale[p] = mp[p] == m ? 1.f : none ? 0.f : fast_exp2(mp[p] - m);
-      l += none ? 0.f : scale[p] * lp[p];
+      scale[p] = mp[p] == m ? 1.f : fast_exp2(mp[p] - m);
+      l = fmaf(scale[p], lp[p], l);
     }
   }
   if (!kOneRound) {
@@ -559,7 +571,7 @@ __device__ __forceinline__ void merge_parts(f32x16 (&o)[D / 32], float& m, float
 #pragma unroll
     for (int dg = 0; dg < D / 32; ++dg)
 #pragma unroll
-      for (int e = 0; e < 16; ++e) o[dg][e] = scale[0] == 0.f ? 0.f : o[dg][e] * scale[0];
+      for (int e = 0; e < 16; ++e) o[dg][e] *= scale[0];
 #pragma unroll
     for (int p = 1; p < PARTS; ++p)
 #pragma unroll
@@ -567,9 +579,7 @@ __device__ __forceinline__ void merge_parts(f32x16 (&o)[D / 32], float& m, float
         const f32x4 x = *(const SA_LDS f32x4*)(sums(p) + i * 1024);
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          o[i / 4][4 * (i % 4) + e] =
-              scale[p] == 0.f ? o[i / 4][4 * (i % 4) + e]
-                              : fmaf(scale[p], x[e], o[i / 4][4 * (i % 4) + e]);
+          o[i / 4][4 * (i % 4) + e] = fmaf(scale[p], x[e], o[i / 4][4 * (i % 4) + e]);
       }
   }
   barrier_lds_reads_done();  // the tiles are free again

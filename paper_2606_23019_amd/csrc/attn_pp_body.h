@@ -274,6 +274,7 @@
 #pragma unroll
         for (int dg = 0; dg < D / 32; ++dg) o[dg] *= alpha;
       }
+      const float m_exp = PARTS > 1 ? fmaxf(m_run, part_floor<PARTS>(part)) : m_run;
       float lsum = 0.f;
 #pragma unroll
       for (int kg = 0; kg < BK / 32; ++kg)
@@ -281,7 +282,7 @@
         for (int j8 = 0; j8 < 2; ++j8)
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
-            const float p = fast_exp2(fmaf(s[kg][8 * j8 + e], c_log2, -m_run));
+            const float p = fast_exp2(fmaf(s[kg][8 * j8 + e], c_log2, -m_exp));
             lsum += p;
             pf[2 * kg + j8][e] = (__bf16)p;
           }

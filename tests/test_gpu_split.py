@@ -82,6 +82,92 @@ def test_part_of_infinitely_low_logits_adds_nothing(N, blk, d):
     compare(out.float().cpu().numpy(), lse.cpu().numpy(), *ref)
 
 
+def _attend(call, q, k, v, rows, blk):
+    from paper_2606_23019_amd import binding
+    B, H, N, _ = q.shape
+    if call == "dense":
+        return binding.dense_attn_fwd(q, k, v, blk)
+    if call == "oneshot":  # walks the mask where one item fills a workgroup
+        return binding.bsattn_fwd(q, k, v, pack_rows(rows), blk, blk)
+    return binding.Plan(pack_rows(rows), B, H, N, blk, blk)(q, k, v)
+
+
+NON_FINITE = [
+    # (call, H, N, d, blk): two and four parts, off the mask, off the list and maskless
+    ("oneshot", 1, 1000, 128, 128), ("plan", 1, 1000, 128, 128), ("dense", 1, 1000, 128, 128),
+    ("oneshot", 1, 2050, 64, 64), ("plan", 1, 2050, 64, 64), ("dense", 1, 2050, 64, 64),
+    ("plan", 9, 2050, 64, 64),
+    ("dense", 57, 1100, 64, 128),  # a shared last round
+    ("plan", 57, 1100, 64, 128),   # not shared
+]
+
+
+@pytest.mark.parametrize("call,H,N,d,blk", NON_FINITE)
+def test_nan_in_any_part_reaches_the_output(call, H, N, d, blk):
+    # a run of key blocks with NaN keys, or with NaN values that weigh nothing: parts of their
+    # own, or the first, middle or last blocks of a part
+    import torch
+    n = -(-N // blk)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn((1, H, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    q[..., 0] = 1.0
+    rng = np.random.default_rng(N)
+    for at, end in ((0, 1), (1, 2), (n // 2, n // 2 + 1), (n - 1, n), ((n + 1) // 2, n),
+                    (0, (n + 1) // 2), (n - n // 4, n)):
+        rows = np.ones((H, n, n), dtype=bool)
+        if call != "dense":
+            others = rng.permutation(np.delete(np.arange(n), np.arange(at, end)))
+            rows[:, 1:5] = False
+            rows[:, 1, list(others[:3]) + [at]] = True  # four blocks, one of them bad
+            rows[:, 2, [others[0], at]] = True          # two
+            rows[:, 3, at] = True                       # alone
+            rows[:, 4, others] = True                   # none of them bad
+        hit = np.repeat(rows[0, :, at:end].any(-1), blk)[:N]
+        keys = slice(at * blk, min(end * blk, N))
+        clean, clean_lse = _attend(call, q, k, v, rows, blk)
+        bad = k.clone()
+        bad[:, :, keys] = torch.nan
+        out, lse = _attend(call, q, bad, v, rows, blk)
+        on = torch.from_numpy(hit).cuda()
+        assert torch.isnan(out[:, :, on]).all() and not torch.isfinite(lse[:, :, on]).any(), at
+        assert torch.equal(out[:, :, ~on], clean[:, :, ~on])
+        assert torch.equal(lse[:, :, ~on], clean_lse[:, :, ~on])
+        # a channel of NaN values: 0 times NaN, whatever the block's weight
+        low = k.clone()
+        low[:, :, keys, 0] = -2e4
+        bad = v.clone()
+        bad[:, :, keys, 3] = torch.nan
+        out, _ = _attend(call, q, low, bad, rows, blk)
+        want, _ = _attend(call, q, low, v, rows, blk)
+        assert torch.isnan(out[:, :, on, 3]).all(), at
+        bad_at = torch.isnan(out)
+        bad_at[:, :, on, 3] = False
+        assert not bad_at.any()
+        assert torch.equal(out[..., 4:], want[..., 4:])
+
+
+@pytest.mark.parametrize("call,H,N,d,blk", NON_FINITE)
+def test_any_block_of_infinitely_low_logits_but_the_first_adds_nothing(call, H, N, d, blk):
+    import torch
+    n = -(-N // blk)
+    g = torch.Generator(device="cuda").manual_seed(N + 1)
+    q, k, v = (torch.randn((1, H, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    q[..., 0] = q[..., 0].abs() + 1.0
+    heads = [0, H - 1]
+    for at in sorted({1, n // 4, n // 2, n - 2, n - 1}):
+        rows = np.ones((H, n, n), dtype=bool)
+        keys = slice(at * blk, min((at + 1) * blk, N))
+        low = k.clone()
+        low[:, :, keys, 0] = -torch.inf
+        out, lse = _attend(call, q, low, v, rows, blk)
+        rows = rows[heads]
+        rows[:, :, at] = False
+        low[:, :, keys] = 0.0
+        ref = oracle.attention(*(to_bits(x[:, heads]) for x in (q, low, v)), pack_rows(rows), blk,
+                               blk, d ** -0.5)
+        compare(out[:, heads].float().cpu().numpy(), lse[:, heads].cpu().numpy(), *ref)
+
+
 def test_wide_tiles_of_the_maskless_path_match_reference():
     # blocks of 64 that would run unshared take 128 x 128 tiles from 512 tokens on
     import torch
