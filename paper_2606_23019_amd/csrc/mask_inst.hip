@@ -111,19 +111,29 @@ constexpr int kInstManyMin = 6;
 constexpr int kInstManyWaves = 4;
 constexpr int kInstManyResident = 4;  // wavefronts a SIMD
 
-// For k = 15 .. 0: acc = 2 acc + (t[k] <= p).  One statement, so that nothing
-// is put between the pairs.
+// For k = 15 .. 0: acc = 2 acc + (t[k] <= p).  A vector read of a vector-written
+// scalar needs two wait states, so the compares rotate over three pairs of
+// scalars and every carry is added two compares after its own; one statement,
+// since that order is what keeps the distance.
 __device__ __forceinline__ void push16(uint32_t& acc, const float* t, float p) {
-#define SA_PUSH(n) "v_cmp_le_f32 vcc, %" #n ", %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
-  asm(SA_PUSH(17) SA_PUSH(16) SA_PUSH(15) SA_PUSH(14) SA_PUSH(13) SA_PUSH(12) SA_PUSH(11)
-          SA_PUSH(10) SA_PUSH(9) SA_PUSH(8) SA_PUSH(7) SA_PUSH(6) SA_PUSH(5) SA_PUSH(4) SA_PUSH(3)
-              SA_PUSH(2)
-      : "+v"(acc)
+  uint64_t c0, c1;
+#define SA_CMP(c, n) "v_cmp_le_f32 " c ", %" #n ", %3\n\t"
+#define SA_ADD(c) "v_addc_co_u32 %0, " c ", %0, %0, " c "\n\t"
+#define SA_STEP(c, n) SA_ADD(c) SA_CMP(c, n)
+  asm(SA_CMP("vcc", 19) SA_CMP("%1", 18) SA_CMP("%2", 17)
+          SA_STEP("vcc", 16) SA_STEP("%1", 15) SA_STEP("%2", 14)
+          SA_STEP("vcc", 13) SA_STEP("%1", 12) SA_STEP("%2", 11)
+          SA_STEP("vcc", 10) SA_STEP("%1", 9) SA_STEP("%2", 8)
+          SA_STEP("vcc", 7) SA_STEP("%1", 6) SA_STEP("%2", 5)
+          SA_STEP("vcc", 4) SA_ADD("%1") SA_ADD("%2") SA_ADD("vcc")
+      : "+&v"(acc), "=&s"(c0), "=&s"(c1)
       : "v"(p), "v"(t[0]), "v"(t[1]), "v"(t[2]), "v"(t[3]), "v"(t[4]), "v"(t[5]), "v"(t[6]),
         "v"(t[7]), "v"(t[8]), "v"(t[9]), "v"(t[10]), "v"(t[11]), "v"(t[12]), "v"(t[13]),
         "v"(t[14]), "v"(t[15])
       : "vcc");
-#undef SA_PUSH
+#undef SA_STEP
+#undef SA_ADD
+#undef SA_CMP
 }
 
 // Where lane l's half word f is in the map.
