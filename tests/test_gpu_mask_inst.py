@@ -67,8 +67,8 @@ MANY = [
     (1, 1, 32, 6, 20),      # one half word with entries and one without
     (3, 7, 31, 6, 21),      # rows too short for it
     (3, 7, 33, 7, 22),      # a half word of one block, read from 31 blocks earlier
-    (5, 13, 95, 20, 23),    # one staged chunk of thresholds; heads change inside a wavefront
-    (40, 2, 64, 21, 24),    # a chunk and one more; a head every four half words
+    (5, 13, 95, 20, 23),    # three parts of 7, 7 and 6; heads change inside a wavefront
+    (40, 2, 64, 21, 24),    # three parts of 7; a head every four half words
     (2, 33, 97, 64, 25),    # a half word past the row's end that reads none of its entries
     (4, 256, 300, 9, 26),   # sets cut in no parts
     (16, 591, 591, 13, 27),  # several groups a wavefront
@@ -88,6 +88,33 @@ def test_instantiate_many_thresholds_bit_exact(H, n_qb, n_kb, n_p, seed):
     p.reshape(-1)[::5] *= -1.0
     p.reshape(-1)[1::9] = np.nan
     p.reshape(-1)[2::13] = np.inf
+    assert np.array_equal(_run(T, p), oracle.instantiate_packed(T, p))
+
+
+@pytest.mark.parametrize("H,n_qb,n_kb,n_p", [
+    # parts of more thresholds than the kernel stages at a time (20): so many half words that a
+    # set is cut in few parts, and a wavefront takes several groups of them
+    (40, 6600, 40, 20),   # one part, just staged at once
+    (40, 6600, 40, 21),   # one part: a chunk and one more
+    (40, 6600, 33, 41),   # one part: two chunks and one more
+    (40, 4500, 64, 50),   # two parts of 25
+])
+def test_instantiate_parts_of_several_chunks_bit_exact(H, n_qb, n_kb, n_p):
+    rng = np.random.default_rng(n_p)
+    T = rng.random((H, n_qb, n_kb), dtype=np.float32)
+    T.reshape(-1)[3::11] = np.nan
+    p = rng.random((n_p, H), dtype=np.float32)
+    got = _run(T, p)
+    for i in range(n_p):
+        assert np.array_equal(got[i], oracle.instantiate_packed(T, p[i:i + 1])[0]), i
+
+
+@pytest.mark.parametrize("n_kb,n_p", [(31, 17), (20, 50), (1, 16)])
+def test_instantiate_short_rows_of_many_thresholds_bit_exact(n_kb, n_p):
+    # rows too short for the many-threshold kernel: sets of 16 over the grid
+    rng = np.random.default_rng(n_kb)
+    T = rng.random((3, 9, n_kb)).astype(np.float32)
+    p = rng.random((n_p, 3)).astype(np.float32)
     assert np.array_equal(_run(T, p), oracle.instantiate_packed(T, p))
 
 
