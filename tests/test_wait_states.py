@@ -6,7 +6,10 @@ the two, but does not look into inline assembly.  Each source is compiled to ass
 pair that needs a distance is checked in the order of the listing, whoever wrote it:
 
   * a vector instruction that reads a scalar (vcc or s registers) written by a vector
-    instruction: two wait states.
+    instruction: two wait states;
+  * a vector-memory instruction whose address or data scalars were written by a vector
+    instruction: five;
+  * a load that goes directly to LDS after a write of m0, its address there: one.
 """
 
 import os
@@ -63,14 +66,20 @@ def too_soon(text):
     """Pairs with fewer wait states between them than they need."""
     found = []
     written = {}  # scalar -> wait states since a vector instruction wrote it
+    m0 = 9        # wait states since m0 was written
     where = None
     for name, line, op, args in instructions(text):
         if name != where:
-            written, where = {}, name
+            written, m0, where = {}, 9, name
         if op.startswith("v_"):
             if any(written.get(r, 9) < 2 for r in vector_reads(op, args)):
                 found.append((name, line, op, args))
+        elif op.startswith(("global_", "buffer_", "flat_", "scratch_")):
+            used = set().union(*[scalars(a.split()[0]) for a in args if a.strip()])
+            if any(written.get(r, 9) < 5 for r in used) or ("_lds_" in op and m0 < 1):
+                found.append((name, line, op, args))
         states = int(args[0], 0) + 1 if op == "s_nop" else 1
+        m0 += states
         for r in written:
             written[r] += states
         if op.startswith("v_"):
@@ -79,6 +88,8 @@ def too_soon(text):
         elif op.startswith("s_") and args and not op.startswith(("s_cmp", "s_nop", "s_bitcmp")):
             for r in scalars(args[0]):
                 written.pop(r, None)  # rewritten by a scalar instruction
+            if "m0" in scalars(args[0]):
+                m0 = 0
     return found
 
 
@@ -103,6 +114,12 @@ def test_the_check_sees_what_it_looks_for():
     assert one("v_cmp_le_f32_e64 s[4:5], v1, v2", other, "v_cndmask_b32_e64 v0, v1, v2, s[4:5]") == 1
     assert one("v_readlane_b32 s7, v1, 3", "v_add_u32_e32 v1, s7, v1") == 1
     assert one("v_readlane_b32 s7, v1, 3", "v_add_u32_e32 v1, s8, v1") == 0
+    load = "global_load_lds_dwordx4 v2, s[6:7]"
+    assert one("s_mov_b32 m0, s3", load) == 1 and one("s_add_i32 m0, s3, 0x400", load) == 1
+    assert one("s_mov_b32 m0, s3", "s_nop 0", load) == 0
+    assert one("s_mov_b32 m0, s3", "global_load_dword v2, v3, s[6:7]") == 0
+    assert one("v_readfirstlane_b32 s7, v1", "s_nop 3", load) == 1
+    assert one("v_readfirstlane_b32 s7, v1", "s_nop 4", load) == 0
 
 
 @pytest.mark.parametrize("source", ["prepass.hip", "mask_inst.hip", "fidelity.hip", "resize.hip",
