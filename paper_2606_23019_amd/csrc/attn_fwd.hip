@@ -497,6 +497,16 @@ struct PingPong {
 template <int BQ, int BK, int D, bool DENSE>
 constexpr bool kUsePingPong = PingPong<BQ, BK, D>::kFits && (BQ == 128 || DENSE);
 
+// Rows of up to this many key blocks are walked by their first part alone, and
+// a workgroup with no others has nothing to put together, which takes 0.5-1.8
+// us.  Kernels of rows of 1 / 2 / 3 / 4 blocks, us, without this rule -> with it
+// (and not shared): 64 x 64, d = 128, 1 head x 512 tokens 7.4 / 7.5 / 8.3 / 8.5 ->
+// 5.6 / 7.0 / 8.3 / 8.5 (5.0 / 6.4 / 7.7 / 9.1); 128 x 128, d = 128, 12 x 1024 7.9 /
+// 9.3 / 11.1 / 12.7 -> 6.9 / 9.2 / 11.0 / 12.6 (9.1 / 11.8 / 14.8 / 17.9).  With
+// rows of three walked alone too, those take 0.1-0.9 us more.
+template <int PARTS>
+constexpr int kAlone = PARTS > 1 ? 2 : 0;
+
 // What stands for a maximum of -inf in the exponents of part `part`.  A walk
 // over all blocks has a finite maximum when it comes to a block whose logits
 // are all -inf, and gives it weights of 0, unless that is its first block,
@@ -672,8 +682,13 @@ __global__ __launch_bounds__(512, 1) void bsattn_mask_split_kernel(SA_PP_PARAMS)
 //   64 x 64, four: maskless 1 x 16000 429 -> 156, masked 64 -> 32; two: 4 x
 //   8000 228 -> 149 and 132 -> 98.
 // One item a workgroup without sharing it gained 5-10 %; past the line sharing
-// would cost two rounds of halves for one of pairs.  Short rows have little to
-// share: four parts of 16 blocks at 0.3 density took 8.4 us for 7.7.
+// would cost two rounds of halves for one of pairs.  Rows of 8 key blocks are
+// the shortest shared: kernels of a plan, not shared -> shared, us, at densities
+// 0.1 / 0.3 / 0.6, 64 x 64, d = 64, 8 heads x 512 tokens 7.4 / 8.7 / 12.0 -> 6.2 /
+// 6.8 / 7.4; d = 128, 1 x 512 6.2 / 9.0 / 11.8 -> 7.4 / 8.4 / 9.8 before kAlone, 1 x
+// 1024 (16 blocks) 9.1 / 15.9 / 21.5 -> 8.5 / 11.4 / 13.3.  (Maskless tiles of 64
+// with d = 64 leave room for a second workgroup on a compute unit, with 126
+// registers a lane; masked ones take 146.  The rule counts on one.)
 constexpr int kCus = 32;  // compute units of an XCD
 
 inline int parts_of(int64_t seq, int slots, int n_kb) {

@@ -93,17 +93,19 @@
   int first = FROM_MASK ? 0 : kblk(0);  // in range for every row (n_kb >= 1): read before cnt is known
   asm volatile("" : "+s"(first));     // keeps that load here, not inside the cnt > 0 branch
   __builtin_amdgcn_sched_barrier(0);  // counts and the first key block issued together
-  // every item's count: all groups run max(counts) iterations
+  // every item's count: all groups run as many iterations as the longest walk takes
+  auto run_of = [&](int c) { return c > kAlone<PARTS> ? (c + PARTS - 1) / PARTS : c; };
   int cnt = 0, n_iter = 0;
+  bool shared = false;  // an item of this workgroup is
 #pragma unroll
   for (int sl = 0; sl < kItems; ++sl) {
     const int c = pos_of(sl) < n_items ? min(max(c_of[sl], 0), n_kb) : 0;
-    n_iter = max(n_iter, c);
+    n_iter = max(n_iter, run_of(c));
+    if (PARTS > 1 && c > kAlone<PARTS>) shared = true;
     if (sl == mine) cnt = c;
   }
   if constexpr (PARTS > 1) {
-    n_iter = (n_iter + PARTS - 1) / PARTS;
-    const int run = (cnt + PARTS - 1) / PARTS;
+    const int run = run_of(cnt);
     t0 = min(part * run, cnt);
     cnt = min(run, cnt - t0);
     if constexpr (FROM_MASK) {
@@ -294,8 +296,9 @@
 
   float l_tot = pair_sum(l_run);
   if constexpr (PARTS > 1)
-    merge_parts<PARTS, kItems * T::kWaves, D, (int)sizeof(Ks_all)>(
-        o, m_run, l_tot, (char*)Ks_all, (char*)Vs_all, part, mine * T::kWaves + gwave_u, lane);
+    if (shared)
+      merge_parts<PARTS, kItems * T::kWaves, D, (int)sizeof(Ks_all)>(
+          o, m_run, l_tot, (char*)Ks_all, (char*)Vs_all, part, mine * T::kWaves + gwave_u, lane);
   const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
   const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   const int l32_e = lane_e & 31;
