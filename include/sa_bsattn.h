@@ -237,10 +237,15 @@ SA_API int sa_bsattn_fwd_prepared(const void* q, const void* k, const void* v,
  * no mask machinery (no pre-pass, no schedule, no workspace, no allocation).
  * It is the 0 %-sparsity baseline against which the CRM path's overhead is
  * measured (the paper's appendix "Detailed Kernel Overhead Analysis" compares
- * its kernel at 0 % sparsity with a dense FlashAttention kernel).  The result
- * equals sa_bsattn_fwd with an all-ones mask bit for bit.  blk is the tile
- * size (64 or 128, used for both query and key blocks).  Arguments and errors otherwise as
- * sa_bsattn_fwd.
+ * its kernel at 0 % sparsity with a dense FlashAttention kernel).  blk is the
+ * tile size (64 or 128, used for both query and key blocks) that a mask would
+ * have.  The result equals sa_bsattn_fwd with an all-ones mask bit for bit up
+ * to 512 query blocks (B H ceil(N / blk)), and for any number of them while N
+ * < 512 (blk 64) or N <= 896 (blk 128).  Beyond that, where no mask depends on
+ * the tiles, blk 64 may be computed in tiles of 128, and the key blocks of the
+ * last query blocks in two parts: the result then agrees with the masked call
+ * to within the order of the fp32 sums and the bf16 rounding of the
+ * probabilities.  Arguments and errors otherwise as sa_bsattn_fwd.
  */
 SA_API int sa_dense_attn_fwd(const void* q, const void* k, const void* v, void* out, float* lse,
                              int B, int H, int N, int d, int blk, float scale, void* stream);

@@ -231,7 +231,10 @@ def bsattn_fwd_bnhd(q, k, v, mask_bits, blk_q, blk_k, scale=None, out=None, lse=
 
 
 def dense_attn_fwd(q, k, v, blk=128, scale=None, out=None, lse=None, stream=None):
-    """``sa_dense_attn_fwd``: maskless attention (every key block enabled)."""
+    """``sa_dense_attn_fwd``: maskless attention (every key block enabled).
+
+    Up to 512 query blocks over batches and heads the bits of ``bsattn_fwd`` with an all-ones
+    mask; beyond, its result to within rounding (the header gives the line)."""
     torch = _torch()
     lib = load()
     B, H, N, d = q.shape

@@ -675,8 +675,10 @@ __global__ __launch_bounds__(512, 1) void bsattn_mask_split_kernel(SA_PP_PARAMS)
 // (masked items of 64 rows: up to four workgroups of one).  A problem that
 // does not fill them leaves units and groups idle, so its items are shared by
 // the groups of a workgroup instead, as many to an item as there are compute
-// units for.  The rule goes by the shape alone, so that every entry point and
-// order gives the same bits.  Measured, d = 128, start -> shared, us:
+// units for.  The rule goes by the shape alone, so that every masked entry
+// point and order gives the same bits, and so does the maskless one, up to the
+// 512 items from which it has rules of its own (shared_rest, wide tiles).
+// Measured, d = 128, start -> shared, us:
 //   128 x 128, two parts: maskless 1 head x 16000 tokens 332 -> 175, 2 x 16000
 //   337 -> 236; masked 2 x 8000 132 -> 75, 3 x 2000 39 -> 24;
 //   64 x 64, four: maskless 1 x 16000 429 -> 156, masked 64 -> 32; two: 4 x

@@ -236,3 +236,30 @@ def test_walk_off_the_mask_gives_the_bits_of_the_list(H, N, d, blk_q, blk_k, p):
     t = [x.transpose(1, 2).contiguous() for x in (q, k, v)]
     out, lse = binding.bsattn_fwd_bnhd(*t, noisy, blk_q, blk_k)
     assert torch.equal(out.transpose(1, 2), plan(q, k, v)[0]) and torch.equal(lse, want_lse)
+
+
+@pytest.mark.parametrize("B,H,N,d,blk,same", [
+    (1, 16, 4096, 64, 128, True),     # 512 query blocks
+    (2, 16, 1000, 128, 64, True),     # 512
+    (1, 74, 896, 64, 128, True),      # 518, of 7 key blocks
+    (1, 66, 511, 64, 64, True),       # 528, under 512 tokens
+    (1, 57, 1100, 64, 128, False),    # 513 query blocks: a shared last round
+    (1, 65, 512, 64, 64, False),      # 520: tiles of 128
+    (1, 57, 1030, 128, 64, False),    # both
+])
+def test_maskless_and_all_ones_mask_on_both_sides_of_the_line(B, H, N, d, blk, same):
+    # bit for bit up to 512 query blocks, or 511 (blk 64) and 896 (blk 128) tokens; beyond, to
+    # within the rounding that the reference comparison allows either of them
+    import torch
+    from paper_2606_23019_amd import binding
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn((B, H, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+    n = -(-N // blk)
+    ones = pack_rows(np.ones((H, n, n), dtype=bool))
+    out, lse = binding.dense_attn_fwd(q, k, v, blk)
+    want, want_lse = binding.bsattn_fwd(q, k, v, ones, blk, blk)
+    if same:
+        assert torch.equal(out, want) and torch.equal(lse, want_lse)
+    else:
+        compare(out.float().cpu().numpy(), lse.cpu().numpy(), want.float().cpu().numpy(),
+                want_lse.cpu().numpy())
