@@ -67,9 +67,16 @@ SA_API int sa_version(void);
  * One-shot forward pass (Sec. 4.3.2): runs the mask pre-pass, the schedule
  * and the attention kernel on `stream`.  Internal workspace (per-row counts
  * and key-block lists, the work order) is taken with stream-ordered
- * hipMallocAsync and released with hipFreeAsync on the same stream.  Shapes
- * whose query blocks all run at once (up to 256 of them over the heads, 8 or
- * more key blocks) need neither: their attention kernel reads the mask itself.
+ * hipMallocAsync and released with hipFreeAsync on the same stream.  Calls of
+ * up to 256 query blocks (B H n_qb) and 8 to 512 key blocks need neither,
+ * other than 64 x 128 blocks at d = 128: their attention kernel reads the mask
+ * itself.
+ * Every masked entry point gives the same bits for the same call.  They are
+ * those of one walk over a query block's key blocks or of several put
+ * together, by a rule on the whole call's shape (B H n_qb and n_kb) and the
+ * number of key blocks in the row.  The same head in a call of more or fewer
+ * heads or batches may so differ in the order of its fp32 sums and in the
+ * bf16 rounding of the probabilities that follows from it, not in precision.
  * Returns SA_OK, SA_ERR_INVALID_ARG, SA_ERR_UNSUPPORTED or SA_ERR_HIP.
  */
 SA_API int sa_bsattn_fwd(const void* q, const void* k, const void* v,

@@ -263,3 +263,25 @@ def test_maskless_and_all_ones_mask_on_both_sides_of_the_line(B, H, N, d, blk, s
     else:
         compare(out.float().cpu().numpy(), lse.cpu().numpy(), want.float().cpu().numpy(),
                 want_lse.cpu().numpy())
+
+
+@pytest.mark.parametrize("N,d,blk", [(2000, 128, 128), (1500, 64, 64)])
+def test_a_head_in_calls_of_more_heads(N, d, blk):
+    # shared by a rule on the whole call's shape: the same bits while the rule says the same, the
+    # same result to within rounding where it does not
+    import torch
+    from paper_2606_23019_amd import binding
+    H = 40
+    n = -(-N // blk)
+    mask = np.random.default_rng(N).random((H, n, n)) < 0.3
+    g = torch.Generator(device="cuda").manual_seed(N)
+    q, k, v = (torch.randn((1, H, N, d), generator=g, device="cuda").bfloat16() for _ in range(3))
+
+    def of(heads):
+        o, l = binding.bsattn_fwd(*(x[:, :heads].contiguous() for x in (q, k, v)),
+                                  pack_rows(mask[:heads]), blk, blk)
+        return o[:, :1], l[:, :1]
+    alone, few, all_ = of(1), of(4), of(H)  # 16 or 24, 64 or 96, 640 or 960 query blocks
+    assert torch.equal(alone[0], few[0]) and torch.equal(alone[1], few[1])
+    compare(alone[0].float().cpu().numpy(), alone[1].cpu().numpy(), all_[0].float().cpu().numpy(),
+            all_[1].cpu().numpy())
