@@ -21,7 +21,7 @@ def split_kernels(tmp_path_factory):
         "-I", os.path.join(ROOT, "include"), "-I", os.path.dirname(SRC), "--cuda-device-only", "-S",
         "-o", out, SRC], check=True, capture_output=True)
     text = open(out).read()
-    names = sorted(set(re.findall(r"^(_ZN2sa\S+bsattn_split_kernel\S+):", text, re.M)))
+    names = sorted(set(re.findall(r"^(_ZN2sa\S+bsattn_(?:mask_)?split_kernel\S+):", text, re.M)))
     code = {n: text[text.index("\n%s:" % n):] for n in names}
     code = {n: c[:c.index(".Lfunc_end")].split("\n") for n, c in code.items()}
     meta = {re.search(r"\.name:\s+(\S+)", b).group(1): b
@@ -34,7 +34,10 @@ def test_split_kernels_found(split_kernels):
     # 128-row items in two parts: two key block sizes x two head dims, bf16 or fp32 out, and the
     # square ones maskless; 64-row items in two and four: (64, 64) x two head dims and (64, 128)
     # with d = 64, bf16 or fp32 out, and the square ones maskless
-    assert len(code) == (4 * 2 + 2) + 2 * (3 * 2 + 2), sorted(code)
+    walks = [n for n in code if "mask_split" in n]
+    assert len(code) - len(walks) == (4 * 2 + 2) + 2 * (3 * 2 + 2), sorted(code)
+    # the walk off the mask, one item a workgroup: the masked ones in two and four parts
+    assert len(walks) == 4 * 2 + 3 * 2, walks
 
 
 def test_split_kernels_keep_no_scratch_and_only_copies_in_loops(split_kernels):
