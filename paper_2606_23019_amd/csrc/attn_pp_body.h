@@ -295,12 +295,13 @@
   if (grp == 0) barrier_lds_reads_done();  // matches the second group's extra barrier
 
   float l_tot = pair_sum(l_run);
+  const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   if constexpr (PARTS > 1)
     if (shared)
       merge_parts<PARTS, kItems * T::kWaves, D, (int)sizeof(Ks_all)>(
-          o, m_run, l_tot, (char*)Ks_all, (char*)Vs_all, part, mine * T::kWaves + gwave_u, lane);
+          o, m_run, l_tot, (char*)Ks_all, (char*)Vs_all, part, mine * T::kWaves + gwave_u,
+          lane_e);
   const float inv = l_tot > 0.f ? 1.0f / l_tot : 0.f;
-  const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
   const int l32_e = lane_e & 31;
   const int half_e = lane_e >> 5;
   const int row0 = u * BQ + gwave_u * 32;

@@ -45,11 +45,19 @@ def test_split_kernels_keep_no_scratch_and_only_copies_in_loops(split_kernels):
     for name, lines in code.items():
         for key in ("vgpr_spill_count", "private_segment_fixed_size"):
             assert int(re.search(r"\.%s:\s+(\d+)" % key, meta[name]).group(1)) == 0, (name, key)
-        marked = [i for i, l in enumerate(lines) if "in Loop:" in l or "Loop Header" in l]
-        assert marked, name
-        hi = max(marked) + 1
-        while hi < len(lines) and not re.match(r"^\.LBB", lines[hi]):
-            hi += 1
-        ops = Counter(l.split()[0] for l in lines[min(marked):hi]
+        # the outermost loops; the one over key blocks has the most lines, those before it walk
+        # the mask row (Q's loads may stand between)
+        spans = []
+        for i, line in enumerate(lines):
+            m = re.match(r"^\.L(BB\d+_\d+):.*Loop Header: Depth=1", line)
+            if m:
+                at = [j for j, l in enumerate(lines) if "Header=%s " % m.group(1) in l] + [i]
+                hi = max(at) + 1
+                while hi < len(lines) and not re.match(r"^\.LBB|^; %bb", lines[hi]):
+                    hi += 1
+                spans.append(lines[min(at):hi])
+        inside = max(spans, key=len)
+        assert any("v_mfma" in l for l in inside) and any("v_exp" in l for l in inside), name
+        ops = Counter(l.split()[0] for l in inside
                       if re.match(r"^\s+(global_|buffer_|scratch_|flat_)", l))
         assert set(ops) == {"global_load_lds_dwordx4"}, (name, dict(ops))
