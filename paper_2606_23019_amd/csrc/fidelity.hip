@@ -139,25 +139,31 @@ __device__ __forceinline__ float wave_sum(float x) {
 constexpr int kFidMaxR = 32;
 constexpr int kFidMaxK = 64;
 
-// One workgroup per (b, h), one wavefront per sampled row at a time.  The row's
-// dense log-normaliser comes from its block log-masses (lanes over blocks).
-// The blocks' masses and map entries then pass through LDS, kRowChunk blocks at
-// a time, one exponential per block; `span` lanes (K rounded up to a power of
-// two) own a candidate each, and the 64 / span groups of lanes share the
-// blocks.  Latency bounds it: with a wavefront's 64 lanes all walking every
-// block and taking its exponential, and the mean in a launch of its own, it
-// took 15.9 us and a launch, 10.4 now (40 heads, 16 rows, 16 candidates, 256
-// blocks; the whole call 89.6 -> 79.4 us).  At the end the rows of the head
-// give its Fidelity Score, 1 - their mean.
+// One workgroup per (b, h), a wavefront for one sampled row or, with NR = 2 for
+// more than kRowWaves of them, for two.  The row's dense log-normaliser comes
+// from its block log-masses (lanes over blocks).  The blocks' masses and map
+// entries then pass through LDS, kRowChunk blocks at a time, one exponential
+// per block; `span` lanes (K rounded up to a power of two) own a candidate
+// each, and the 64 / span groups of lanes share the blocks.  Latency bounds it:
+// with a wavefront's 64 lanes all walking every block and taking its
+// exponential, and the mean in a launch of its own, it took 15.9 us and a
+// launch, 10.4 now (40 heads, 16 rows, 16 candidates, 256 blocks; the whole
+// call 89.6 -> 79.4 us).  For the same reason a wavefront takes its two rows
+// side by side and not in turn: whole calls of 32 rows, 16 candidates, 75600
+// tokens 47.6 -> 43.9 us with one head (44.7 with the kernel for many
+// candidates), 56.1 -> 52.2 with 5 (60.9), 192 -> 187 with 40 (205).  At the end
+// the rows of the head give its Fidelity Score, 1 - their mean.
 constexpr int kRowWaves = 16;
 constexpr int kRowChunk = 256;
 
+template <int NR>
 __global__ __launch_bounds__(64 * kRowWaves) void fid_row_kernel(
     const float* __restrict__ blk_lse, const int32_t* __restrict__ rows, int R,
     const float* __restrict__ T, const float* __restrict__ p, int K, int span, int H, int N,
     int blk, int n_qb, int n_kb, float* __restrict__ hel, float* __restrict__ fid) {
-  __shared__ __attribute__((aligned(16))) float mass_all[kRowWaves][kRowChunk];
-  __shared__ __attribute__((aligned(16))) float map_all[kRowWaves][kRowChunk];
+  static_assert(kFidMaxR <= 2 * kRowWaves, "rows of a head");
+  __shared__ __attribute__((aligned(16))) float mass_all[kRowWaves][NR][kRowChunk];
+  __shared__ __attribute__((aligned(16))) float map_all[kRowWaves][NR][kRowChunk];
   __shared__ float hel_all[kFidMaxR][kFidMaxK];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -167,52 +173,68 @@ __global__ __launch_bounds__(64 * kRowWaves) void fid_row_kernel(
   const int group = lane / span;
   const int groups = 64 / span;
   const float pc = c < K ? p[c] : 0.f;
-  float* mass = mass_all[wave];
-  float* map = map_all[wave];
-  for (int i0 = 0; i0 < R; i0 += kRowWaves) {  // uniform: all wavefronts meet the barriers
-    const int i = min(i0 + wave, R - 1);       // past R: the last row again, not stored
-    const float* lrow = blk_lse + ((int64_t)bh * R + i) * n_kb;
+  const float *lrow[NR], *trow[NR];
+  float mx[NR], z[NR], lse[NR], dropped[NR];
+  bool kept[NR];
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    const int i = min(wave + q * kRowWaves, R - 1);  // past R: the last row again, not stored
+    lrow[q] = blk_lse + ((int64_t)bh * R + i) * n_kb;
     const int r = min(max(rows[(int64_t)h * R + i], 0), N - 1);
-    const float* trow = T + ((int64_t)h * n_qb + r / blk) * n_kb;
-    float mx = -INFINITY;
-    for (int v = lane; v < n_kb; v += 64) mx = fmaxf(mx, lrow[v]);
-    mx = wave_max(mx);
-    float z = 0.f;
-    for (int v = lane; v < n_kb; v += 64) z += __expf(lrow[v] - mx);
-    const float lse = mx + __logf(wave_sum(z));
-    float dropped = 0.f;
-    bool kept = false;
-    for (int v0 = 0; v0 < n_kb; v0 += kRowChunk) {
-      // blocks past the row's end weigh nothing and are off for every candidate
+    trow[q] = T + ((int64_t)h * n_qb + r / blk) * n_kb;
+    mx[q] = -INFINITY;
+    z[q] = dropped[q] = 0.f;
+    kept[q] = false;
+  }
+  for (int v = lane; v < n_kb; v += 64)
+#pragma unroll
+    for (int q = 0; q < NR; ++q) mx[q] = fmaxf(mx[q], lrow[q][v]);
+#pragma unroll
+  for (int q = 0; q < NR; ++q) mx[q] = wave_max(mx[q]);
+  for (int v = lane; v < n_kb; v += 64)
+#pragma unroll
+    for (int q = 0; q < NR; ++q) z[q] += __expf(lrow[q][v] - mx[q]);
+#pragma unroll
+  for (int q = 0; q < NR; ++q) lse[q] = mx[q] + __logf(wave_sum(z[q]));
+  for (int v0 = 0; v0 < n_kb; v0 += kRowChunk) {
+    // blocks past the row's end weigh nothing and are off for every candidate
+#pragma unroll
+    for (int q = 0; q < NR; ++q)
 #pragma unroll
       for (int j = 0; j < kRowChunk / 64; ++j) {
         const int v = v0 + 64 * j + lane;
-        mass[64 * j + lane] = v < n_kb ? __expf(lrow[v] - lse) : 0.f;
-        map[64 * j + lane] = v < n_kb ? trow[v] : NAN;
+        mass_all[wave][q][64 * j + lane] = v < n_kb ? __expf(lrow[q][v] - lse[q]) : 0.f;
+        map_all[wave][q][64 * j + lane] = v < n_kb ? trow[q][v] : NAN;
       }
-      __syncthreads();
-      const int len = min(kRowChunk, n_kb - v0);
+    __syncthreads();
+    const int len = min(kRowChunk, n_kb - v0);
 #pragma unroll 4
-      for (int v = 4 * group; v < len; v += 4 * groups) {  // v + 3 < kRowChunk
-        const f32x4 m = *(const f32x4*)(mass + v);
-        const f32x4 t = *(const f32x4*)(map + v);
+    for (int v = 4 * group; v < len; v += 4 * groups)  // v + 3 < kRowChunk
+#pragma unroll
+      for (int q = 0; q < NR; ++q) {
+        const f32x4 m = *(const f32x4*)(&mass_all[wave][q][v]);
+        const f32x4 t = *(const f32x4*)(&map_all[wave][q][v]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
           const bool on = t[e] <= pc;  // NaN on either side: block off
-          kept = kept || on;
-          dropped += on ? 0.f : m[e];
+          kept[q] = kept[q] || on;
+          dropped[q] += on ? 0.f : m[e];
         }
       }
-      __syncthreads();
-    }
-    int any = kept ? 1 : 0;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < NR; ++q) {
+    int any = kept[q] ? 1 : 0;
+    float d = dropped[q];
     for (int o = span; o < 64; o <<= 1) {
-      dropped += __shfl_xor(dropped, o, 64);
+      d += __shfl_xor(d, o, 64);
       any |= __shfl_xor(any, o, 64);
     }
-    dropped = fminf(fmaxf(dropped, 0.f), 1.f);
-    const float x = any ? sqrtf(dropped / (1.f + sqrtf(1.f - dropped))) : 1.f;
-    if (lane < K && i0 + wave < R) {
+    d = fminf(fmaxf(d, 0.f), 1.f);
+    const float x = any ? sqrtf(d / (1.f + sqrtf(1.f - d))) : 1.f;
+    const int i = wave + q * kRowWaves;
+    if (lane < K && i < R) {
       hel[((int64_t)bh * R + i) * K + lane] = x;
       hel_all[i][lane] = x;
     }
@@ -299,15 +321,19 @@ hipError_t launch_fidelity(const void* q, const void* k, const int32_t* rows, in
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   // With many candidates few groups of lanes are left to share a row's blocks,
-  // and a head's rows on one compute unit wait for its LDS: 40 heads x 75600
-  // tokens, 32 rows, 64 candidates took 228 us a call that way and 211 with a
-  // wavefront of its own for each row over the chip; 5 x 75600, 16 rows, 8
-  // candidates 43 and 68, 40 x 32760, 16 and 16, 79 and 90.
+  // and a head's rows on one compute unit wait for its LDS.  Whole calls, us, in
+  // groups and with a wavefront of its own for each row over the chip: 5 heads x
+  // 75600 tokens, 16 rows, 8 candidates 43 and 68; 40 x 32760, 16 rows, 16
+  // candidates 79 and 90; 17 to 32 candidates 46 and 57 (5 x 75600, 16 rows), 94
+  // and 101 (40 x 32760, 32 rows), but 64 and 61 (5 x 75600, 32 rows), 36.8 and
+  // 33.5 (1 x 32760, 32 rows); 33 to 64 candidates 223 and 209 (40 x 75600, 32
+  // rows), 89 and 64 (5 x 75600).  Up to 16 none is slower in groups.
   int span = 1;
   while (span < K) span *= 2;
   if (span <= 16) {
-    hipLaunchKernelGGL(fid_row_kernel, dim3(B * H), dim3(64 * kRowWaves), 0, stream, blk_lse, rows, R,
-                       T, p, K, span, H, N, blk, n_qb, n_kb, hel, fid);
+    auto kernel = R <= kRowWaves ? fid_row_kernel<1> : fid_row_kernel<2>;
+    hipLaunchKernelGGL(kernel, dim3(B * H), dim3(64 * kRowWaves), 0, stream, blk_lse, rows, R, T, p,
+                       K, span, H, N, blk, n_qb, n_kb, hel, fid);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(fid_row_wide_kernel, dim3(B * H, (R + kFidWaves - 1) / kFidWaves),

@@ -117,10 +117,11 @@ def test_fidelity_full_720p_sampled_heads():
 
 
 @pytest.mark.parametrize("B,H,N,d,blk,R,K,seed", [
-    (1, 1, 16500, 64, 64, 17, 3, 21),   # 258 blocks: a second chunk of two; a second round of one row
+    (1, 1, 16500, 64, 64, 17, 3, 21),   # 258 blocks: a second chunk of two; one wavefront with two rows
     (2, 1, 16384, 64, 64, 32, 16, 22),  # 256 blocks, one whole chunk; the most candidates in groups
     (1, 2, 4100, 64, 64, 16, 1, 23),    # 64 groups of one lane, a ragged last four
     (1, 2, 200, 64, 64, 3, 17, 24),     # a wavefront for a whole row
+    (2, 2, 1000, 64, 64, 31, 16, 25),   # all wavefronts with two rows but one
 ])
 def test_fidelity_rows_in_chunks_and_groups(B, H, N, d, blk, R, K, seed):
     test_fidelity_parity_small(B, H, N, d, blk, R, K, seed)
