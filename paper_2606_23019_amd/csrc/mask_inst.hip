@@ -102,7 +102,10 @@ __global__ __launch_bounds__(64 * kInstWaves) void mask_inst_kernel(
 // and an add-with-carry per block: acc = 2 acc + (t <= p).  That is two
 // instructions per 64 blocks and threshold instead of five issue slots, at the
 // price of a way through LDS for the map entries, so it takes sets of at least
-// kInstManyMin thresholds.  Half words of consecutive lanes are consecutive in
+// kInstManyMin thresholds, from where it is slower at no size measured: here
+// and above, kernel in us, 4 thresholds 14.2 and 15.5 (40 x 591^2), 40 and 47
+// (40 x 1200^2), but 3.6 and 3.4 (12 x 300^2); 6 16.9 and 18.6, 3.8 and 3.8; 8
+// 18.9 and 22.1, 4.1 and 4.3.  Half words of consecutive lanes are consecutive in
 // memory, whatever rows and heads they belong to; a lane reads its own head's
 // threshold.  40 x 591^2 maps, 50 thresholds: 98.4 -> 63 us, of which the
 // comparisons alone are 46 us; without the early requests 67 us (all
@@ -248,9 +251,13 @@ hipError_t launch_mask_instantiate(const float* T, const float* p, int n_p, int 
     const int64_t groups = (rows * (2 * W) + 63) / 64;
     const int64_t places = 4 * 256 * kInstManyResident;
     // a group's thresholds are cut in parts until there are several units for
-    // every place on the chip, but not below kInstManyMin
-    const int64_t cuts = std::min<int64_t>(std::max<int64_t>(1, 4 * places / groups),
-                                           n_p / kInstManyMin);
+    // every place on the chip, but not below kInstManyMin, since each part
+    // loads the entries again; until every SIMD has a unit, down to two (6 and 8
+    // thresholds, kernel in us: 12 x 100^2 maps 3.7 and 4.0 -> 3.0 and 3.0, where
+    // the kernel above takes 3.1 and 3.4; 1 x 591^2 3.7 and 4.0 -> 3.0 and 3.1)
+    const int64_t cuts = std::max(std::min<int64_t>(std::max<int64_t>(1, 4 * places / groups),
+                                                    n_p / kInstManyMin),
+                                  std::min<int64_t>(4 * 256 / groups, n_p / 2));
     const int per_part = (int)((n_p + cuts - 1) / cuts);
     const int n_parts = (n_p + per_part - 1) / per_part;
     const int64_t waves = std::min<int64_t>(groups * n_parts, places);

@@ -67,8 +67,8 @@ MANY = [
     (1, 1, 32, 6, 20),      # one half word with entries and one without
     (3, 7, 31, 6, 21),      # rows too short for it
     (3, 7, 33, 7, 22),      # a half word of one block, read from 31 blocks earlier
-    (5, 13, 95, 20, 23),    # three parts of 7, 7 and 6; heads change inside a wavefront
-    (40, 2, 64, 21, 24),    # three parts of 7; a head every four half words
+    (5, 13, 95, 20, 23),    # ten parts of two thresholds; heads change inside a wavefront
+    (40, 2, 64, 21, 24),    # seven parts of three; a head every four half words
     (2, 33, 97, 64, 25),    # a half word past the row's end that reads none of its entries
     (4, 256, 300, 9, 26),   # sets cut in no parts
     (16, 591, 591, 13, 27),  # several groups a wavefront
