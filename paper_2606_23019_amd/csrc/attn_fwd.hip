@@ -805,8 +805,11 @@ hipError_t launch_attention_dense(const AttnArgs& a, hipStream_t stream) {
   if (a.out_f32) return hipErrorInvalidValue;  // the maskless path writes bf16 only
   // Without a mask the block size is only a tile size.  Where tiles of 64 would
   // run unshared (parts_of), 128 x 128 tiles read half the K and V bytes per
-  // query and are faster (12 heads x 4000 tokens, d = 128: 133 -> 116 us); up
-  // to a few tiles of 64 the padding to 128 would cost more.
+  // query and are faster (12 heads x 4000 tokens, d = 128: 133 -> 116 us).  The
+  // line is where no padding to 128 outweighs that: kernel in us, tiles of 64 and
+  // of 128, d = 64, 65 x 512 20.5 and 15.4, 80 x 520 23.5 and 19.0, 60 x 580 23.9
+  // and 18.5, d = 128 29.8 and 21.2, 35.5 and 27.8, 33.8 and 25.0; below it 100 x
+  // 440 22.2 and 17.5, but 200 x 300 21.1 and 27.4 (d = 128 32.7 and 36.8).
   const int64_t items = (int64_t)a.B * a.H * a.n_qb;
   if (a.blk_q == 64 && a.N >= 512 && parts_of((items + kXcds - 1) / kXcds, 4, a.n_kb) == 1) {
     AttnArgs wide = a;
