@@ -109,13 +109,16 @@ __device__ __forceinline__ float min_canonical(float x, float y) {
 }
 
 constexpr int kStripRows = 15;  // so that its base rows' values fit one 16-register vector
-constexpr int kMapUpWavesMax = 8;
+constexpr int kStripRowsFew = 7;
+constexpr int kMapUpWaves = 8;
+constexpr int kMapUpWavesFew = 16;
 
-__global__ __launch_bounds__(64 * kMapUpWavesMax) void resize_map_up_kernel(
-    const float* __restrict__ T, int nq, int nk, float* __restrict__ out, int tq, int tk) {
+__global__ __launch_bounds__(64 * kMapUpWavesFew) void resize_map_up_kernel(
+    const float* __restrict__ T, int nq, int nk, float* __restrict__ out, int tq, int tk,
+    int strip) {
   const int h = blockIdx.y;
-  const int u0 = blockIdx.x * kStripRows;
-  const int rows = min(kStripRows, tq - u0);
+  const int u0 = blockIdx.x * strip;
+  const int rows = min(strip, tq - u0);
   // the strip's row sample points: lane r holds target row u0 + r's
   const AxisPt a = axis_point(min(u0 + (int)(threadIdx.x & 63), tq - 1), nq, tq, 1.0f / (float)tq);
   const int first = a.i0, second = a.two ? a.i1 : a.i0;
@@ -290,13 +293,22 @@ __global__ __launch_bounds__(64 * kMaskUpWaves) void resize_mask_up_kernel(
 hipError_t launch_resize_map(const float* T, int H, int nq, int nk, float* out, int tq, int tk,
                              hipStream_t stream) {
   if (tq >= nq) {  // a strip of target rows lies on few base rows
-    // as few rounds of up to kMapUpWavesMax wavefronts over the columns as
-    // possible, and no more wavefronts than these rounds need
+    // Where the strips would leave half of the compute units without one, the
+    // time is that of a workgroup, and shorter strips and more wavefronts
+    // shorten it.  Kernel in us, general / strips of 15 / of 7: 1 x 591^2 -> 600^2
+    // 3.9 / 5.4 / 3.6, 1 x 20^2 -> 1200^2 5.5 / 7.1 / 5.3, 40 x (16, 600) -> (16, 640)
+    // 3.9 / 5.4 / 3.7; of 4 3.5, 6.2 and 3.5.  At 192 strips (12 x 60^2 -> 240^2)
+    // 15 and 7 rows take 3.5 both, at 400 (5 x 400^2 -> 450^2) 4.2 and 4.4.
+    const bool few = (int64_t)H * ((tq + kStripRows - 1) / kStripRows) < 128;
+    const int strip = few ? kStripRowsFew : kStripRows;
+    // as few rounds of wavefronts over the columns as possible, and no more
+    // wavefronts than these rounds need
+    const int most = few ? kMapUpWavesFew : kMapUpWaves;
     const int pieces = (tk + 63) / 64;
-    const int rounds = (pieces + kMapUpWavesMax - 1) / kMapUpWavesMax;
-    hipLaunchKernelGGL(resize_map_up_kernel, dim3((tq + kStripRows - 1) / kStripRows, H),
+    const int rounds = (pieces + most - 1) / most;
+    hipLaunchKernelGGL(resize_map_up_kernel, dim3((tq + strip - 1) / strip, H),
                        dim3(64 * ((pieces + rounds - 1) / rounds)), 0, stream, T, nq, nk, out, tq,
-                       tk);
+                       tk, strip);
     return hipGetLastError();
   }
   hipLaunchKernelGGL(resize_map_kernel,

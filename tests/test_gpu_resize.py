@@ -74,15 +74,29 @@ def test_resize_commutes_with_instantiation_on_gpu():
 
 UPSCALE_EDGES = [
     # (H, nq, nk, tq, tk, seed): the upscaling kernels at their edges
-    (2, 15, 64, 15, 64, 20),     # equal sizes: one strip of 15 rows, one word
-    (2, 15, 64, 16, 65, 21),     # a second strip of one row, a second word of one column
-    (1, 30, 95, 31, 96, 22),     # strips over 16 base rows; words over three 32-bit base words
+    (2, 15, 64, 15, 64, 20),     # equal sizes, one word
+    (2, 15, 64, 16, 65, 21),     # a second word of one column
+    (1, 30, 95, 31, 96, 22),     # words over three 32-bit base words
     (3, 29, 128, 30, 129, 23),   # the last strip ends on the last base row
     (1, 7, 33, 150, 1030, 24),   # every target row of a strip on one or two base rows
     (3, 50, 511, 61, 513, 25),   # one column past eight wavefronts; ragged base word
     (5, 9, 2, 13, 700, 26),      # 65 target rows: one past a wavefront of rows
     (1, 12, 40, 5, 90, 27),      # fewer rows, more columns
     (1, 12, 90, 40, 40, 28),     # more rows, fewer columns
+    # map, strips of 7 rows (fewer than 128 of 15)
+    (2, 7, 64, 7, 64, 29),       # one strip
+    (2, 7, 64, 8, 65, 30),       # a second of one row
+    (1, 14, 500, 15, 1024, 31),  # 16 wavefronts of columns
+    (1, 14, 500, 15, 1025, 32),  # one column past
+    (127, 5, 6, 6, 7, 33),       # 127 strips of 15: the last shape with strips of 7
+    # and of 15
+    (128, 5, 6, 6, 7, 34),
+    (128, 15, 64, 15, 64, 35),
+    (64, 15, 64, 16, 65, 36),    # a second strip of one row
+    (43, 30, 95, 31, 96, 37),    # strips over 16 base rows
+    (64, 29, 128, 30, 129, 38),
+    (13, 7, 33, 150, 1030, 39),
+    (26, 50, 511, 61, 513, 40),  # one column past eight wavefronts
 ]
 
 
