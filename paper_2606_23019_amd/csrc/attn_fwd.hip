@@ -97,18 +97,35 @@ __device__ __forceinline__ void barrier_copies_landed() {
   asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(VM) : "memory");
 }
 
-// One wave-wide direct-to-LDS copy: lane l reads 16 bytes at base + voff and
-// writes them to LDS byte address m0 + 16 l.  Issued as inline assembly so
-// that the compiler does not add conservative vmcnt waits before unrelated
-// LDS reads; completion is awaited explicitly with barrier_copies_landed().
-// A direct-to-LDS load needs one wait state after the write of m0, which the
-// compiler does not put ahead of inline assembly (it costs nothing that can be
-// measured: the large masked and maskless calls stay within 0.2 %).
+// Loads J .. J + COUNT - 1 of a group of four wave-wide direct-to-LDS copies: in
+// load j lane l reads 16 bytes at base + off[j] + 1024 j and writes them to LDS
+// byte address m0 + 1024 j + 16 l.  Issued as inline assembly so that the
+// compiler does not add conservative vmcnt waits before unrelated LDS reads;
+// completion is awaited explicitly with barrier_copies_landed().  The
+// instruction's offset counts on both sides, so one write of m0 serves a group.
+// A direct-to-LDS load needs one wait state after that write, which the compiler
+// does not put ahead of inline assembly; with a write and a wait for every load
+// masked items of 64 rows were 1-2 % slower (12 heads x 4000 tokens, d = 64,
+// density 0.3: 43.5 -> 44.2 us, 41.1 in groups).
+template <int J, int COUNT>
 __device__ __forceinline__ void copy16_to_lds(uint32_t lds_byte_addr, const void* base,
-                                              uint32_t voff) {
-  asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               ::"v"(voff), "s"(base), "{m0}"(__builtin_amdgcn_readfirstlane(lds_byte_addr))
-               : "memory");
+                                              const uint32_t (&off)[4]) {
+  const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_byte_addr);
+  if constexpr (COUNT == 4)
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %4 offset:0\n\t"
+                 "global_load_lds_dwordx4 %1, %4 offset:1024\n\t"
+                 "global_load_lds_dwordx4 %2, %4 offset:2048\n\t"
+                 "global_load_lds_dwordx4 %3, %4 offset:3072"
+                 ::"v"(off[0]), "v"(off[1]), "v"(off[2]), "v"(off[3]), "s"(base), "{m0}"(m0)
+                 : "memory");
+  else if constexpr (COUNT == 2)
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %2 offset:%4\n\t"
+                 "global_load_lds_dwordx4 %1, %2 offset:%5"
+                 ::"v"(off[J]), "v"(off[J + 1]), "s"(base), "{m0}"(m0), "n"(1024 * J),
+                 "n"(1024 * J + 1024) : "memory");
+  else
+    asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+                 ::"v"(off[J]), "s"(base), "{m0}"(m0), "n"(1024 * J) : "memory");
 }
 
 // Per-lane byte offsets of a tile copy.  Lane l of load i writes the 16-byte
@@ -121,7 +138,11 @@ __device__ __forceinline__ void copy16_to_lds(uint32_t lds_byte_addr, const void
 // wave + i, and the rest, R n sn elements, is uniform over the wavefront:
 // a plan holds 4 lane offsets, and each load adds its uniform row offset to
 // the scalar base address.  (Every real row is congruent mod 16 to the row
-// used for its swizzle: R (n - n mod 4) is a multiple of 16.)
+// used for its swizzle: R (n - n mod 4) is a multiple of 16.)  The lane offsets
+// also hold 3072 - 1024 (i mod 4), which with the kCopyShift elements that the
+// base addresses given to the copies lie below their tensors takes back the
+// 1024 (i mod 4) of the load instruction (copy16_to_lds).
+constexpr int kCopyShift = 3072 / 2;
 template <typename T, int D>
 struct CopyPlan {
   static constexpr int kRowsPerLoad = 64 / T::kChunksPerRow;
@@ -133,7 +154,7 @@ struct CopyPlan {
       const int lr = lane / T::kChunksPerRow;
       const int p = lane % T::kChunksPerRow;
       const int r = m * kRowsPerLoad + lr;  // row relative to load n - n mod 4
-      lane_off[j] = (uint32_t)(r * sn + ((p ^ swz<D>(r)) << 3)) * 2u;
+      lane_off[j] = (uint32_t)(r * sn + ((p ^ swz<D>(r)) << 3)) * 2u + 1024u * (3 - j);
     }
   }
   // wavefront-uniform byte offset of load i: rows R (n - n mod 4)
@@ -144,7 +165,7 @@ struct CopyPlan {
 };
 
 // Loads i0 .. i0 + count - 1 of a copy of rows key0 .. key0 + BK - 1 (rows sn
-// elements apart) into an LDS tile with global_load_lds_dwordx4 (no
+// elements apart, row 0 at src + kCopyShift) into an LDS tile with global_load_lds_dwordx4 (no
 // registers; completion is tracked by vmcnt).  count and i0 are compile-time
 // constants wherever this is inlined into an unrolled loop.  In a ragged last
 // block, rows past N repeat row N - 1: finite values whose logits are masked
@@ -157,10 +178,17 @@ __device__ __forceinline__ void issue_tile_slice(__bf16* lds, const __bf16* src,
   const uint32_t lds0 =
       (uint32_t)(uintptr_t)(SA_LDS void*)lds + (uint32_t)(wave_u * T::kLoadsPerWave * 1024);
   if (key0 + BK <= N) {
+    const int step = count % 4 ? 2 : 4;  // slices begin at a multiple of their group's length
 #pragma unroll
-    for (int i = i0; i < i0 + count; ++i)
-      copy16_to_lds(lds0 + i * 1024, tile + CopyPlan<T, D>::row_off(wave_u, i, sn),
-                    cp.lane_off[i & 3]);
+    for (int i = i0; i < i0 + count; i += step) {
+      const char* from = tile + CopyPlan<T, D>::row_off(wave_u, i, sn);
+      if (step == 4)
+        copy16_to_lds<0, 4>(lds0 + i * 1024, from, cp.lane_off);
+      else if ((i & 3) == 0)
+        copy16_to_lds<0, 2>(lds0 + i * 1024, from, cp.lane_off);
+      else
+        copy16_to_lds<2, 2>(lds0 + (i & ~3) * 1024, from, cp.lane_off);
+    }
   } else {
     // Row R n + lr of the tile is read from row min(R n + lr, last), addressed
     // from the tile start: lane_off covers rows R (n mod 4) + lr, so the rows
@@ -179,7 +207,15 @@ __device__ __forceinline__ void issue_tile_slice(__bf16* lds, const __bf16* src,
       const int n = wave_u * T::kLoadsPerWave + i;
       constexpr int R = CopyPlan<T, D>::kRowsPerLoad;
       const int rows = min((n & ~3) * R, last - (n & 3) * R - lr);
-      copy16_to_lds(lds0 + i * 1024, tile, cp.lane_off[i & 3] + (uint32_t)(rows * sn) * 2u);
+      uint32_t off[4];
+      off[i & 3] = cp.lane_off[i & 3] + (uint32_t)(rows * sn) * 2u;
+      const uint32_t to = lds0 + (i & ~3) * 1024;
+      switch (i & 3) {
+        case 0: copy16_to_lds<0, 1>(to, tile, off); break;
+        case 1: copy16_to_lds<1, 1>(to, tile, off); break;
+        case 2: copy16_to_lds<2, 1>(to, tile, off); break;
+        default: copy16_to_lds<3, 1>(to, tile, off);
+      }
     }
   }
 }
@@ -310,8 +346,8 @@ __global__ __launch_bounds__(BQ / 32 * 64, (kWavesPerSimd<BQ, BK, D>)) void bsat
   auto kblk = [&](int t) { return DENSE ? t : min(max(list[t], 0), n_kb - 1); };
   const int64_t base = (int64_t)(bh / H) * sb + (int64_t)h * sh;  // element (b, h, token 0, 0)
   const __bf16* Qb = Q + base;
-  const __bf16* Kb = K + base;
-  const __bf16* Vb = V + base;
+  const __bf16* Kb = K + base - kCopyShift;  // read by tile copies only
+  const __bf16* Vb = V + base - kCopyShift;
 
   const int wave_u = __builtin_amdgcn_readfirstlane(wave);
   CopyPlan<T, D> cp;
@@ -349,8 +385,13 @@ __global__ __launch_bounds__(BQ / 32 * 64, (kWavesPerSimd<BQ, BK, D>)) void bsat
   // (its buffer is free once P V[t-1] is done), K[t+1] in two halves inside
   // the softmax of block t (its buffer is free once S[t] is done).  Bursts of
   // copies queue behind each other at issue and hold up the wavefront.
-  constexpr int kVSlice = kL / (BK / 32);
-  static_assert(kL % (BK / 32) == 0 && kL % 2 == 0, "copy slices");
+  // A slice is at least a group of four loads, which take one write of m0 (64 x
+  // 64 blocks, d = 64, slices of two and of four: 12 heads x 4000 tokens 44.3 and
+  // 41.1 us, 10 x 16000 331 and 316, density 0.3; 43.7 and 327 with slices of two
+  // before copies waited for m0).
+  constexpr int kVSlice = kL / (BK / 32) < 4 ? 4 : kL / (BK / 32);
+  constexpr int kKSlice = kL / 2 < 4 ? 4 : kL / 2;
+  static_assert(kL % kVSlice == 0 && kL % kKSlice == 0, "copy slices");
   for (int t = 0; t < cnt; ++t) {
     const int key0 = kblk(t) * BK;
     const bool more = t + 1 < cnt;
@@ -369,7 +410,8 @@ __global__ __launch_bounds__(BQ / 32 * 64, (kWavesPerSimd<BQ, BK, D>)) void bsat
         const bf16x8 a = lds_read_b128(Ks + kr * D + (((2 * dc + half) ^ swz<D>(kr)) << 3));
         s[kg] = mfma32x32x16(a, qf[dc], s[kg]);
       }
-      issue_tile_slice<T, BK, D>(Vs, Vb, key0, N, sn, wave_u, lane, cp, kg * kVSlice, kVSlice);
+      if (kg * kVSlice < kL)
+        issue_tile_slice<T, BK, D>(Vs, Vb, key0, N, sn, wave_u, lane, cp, kg * kVSlice, kVSlice);
     }
 
     barrier_lds_reads_done();  // every wave is done with Ks
@@ -390,7 +432,7 @@ __global__ __launch_bounds__(BQ / 32 * 64, (kWavesPerSimd<BQ, BK, D>)) void bsat
 #pragma unroll
       for (int i = 0; i < 16; ++i) mx = fmaxf(mx, s[kg][i]);
     mx = pair_max(mx) * c_log2;
-    if (more) issue_tile_slice<T, BK, D>(Ks, Kb, key1, N, sn, wave_u, lane, cp, 0, kL / 2);
+    if (more) issue_tile_slice<T, BK, D>(Ks, Kb, key1, N, sn, wave_u, lane, cp, 0, kKSlice);
     // Rescale only when some row's maximum grew.  Keeping the exact running
     // maximum (rather than a stale one) makes each row's largest probability
     // exactly 1, which bf16 represents without error.
@@ -416,8 +458,8 @@ __global__ __launch_bounds__(BQ / 32 * 64, (kWavesPerSimd<BQ, BK, D>)) void bsat
           lsum += p;
           pf[2 * kg + j8][e] = (__bf16)p;
         }
-      if (kg == (BK / 32 - 1) / 2 && more)
-        issue_tile_slice<T, BK, D>(Ks, Kb, key1, N, sn, wave_u, lane, cp, kL / 2, kL / 2);
+      if (kg == (BK / 32 - 1) / 2 && kKSlice < kL && more)
+        issue_tile_slice<T, BK, D>(Ks, Kb, key1, N, sn, wave_u, lane, cp, kKSlice, kKSlice);
     }
     l_run += lsum;
 

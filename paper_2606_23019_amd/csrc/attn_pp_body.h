@@ -134,8 +134,8 @@
 
   const int64_t base = (int64_t)(bh / H) * sb + (int64_t)h * sh;
   const __bf16* Qb = Q + base;
-  const __bf16* Kb = K + base;
-  const __bf16* Vb = V + base;
+  const __bf16* Kb = K + base - kCopyShift;  // read by tile copies only
+  const __bf16* Vb = V + base - kCopyShift;
 
   const int gwave_u = __builtin_amdgcn_readfirstlane(gwave);
   CopyPlan<T, D> cp;
@@ -154,7 +154,7 @@
   const int qrow = u * BQ + gwave * 32 + l32;
   bf16x8 qf[D / 16];
   if constexpr (kStageQ) {
-    issue_tile_copy<T, BK, D>(Vs, Qb, u * BQ, N, sn, gwave_u, lane, cp);
+    issue_tile_copy<T, BK, D>(Vs, Qb - kCopyShift, u * BQ, N, sn, gwave_u, lane, cp);
   } else {
 #pragma unroll
     for (int dc = 0; dc < D / 16; ++dc) {
