@@ -164,6 +164,17 @@ struct CopyPlan {
   }
 };
 
+// Whether the loads of a group are issued one by one (one write of m0, but a
+// wait each) instead of in one statement.  Masked items of 64 rows at d = 128
+// stream the most tile bytes per flop, and where most of those miss in L2 a
+// burst of four waits longer than four loads apart: 20 heads x 67609 tokens,
+// unstructured masks, density 0.16, in bursts and one by one 11.22 and 10.96 ms
+// (10.93 before copies waited for m0), 40 heads at 0.08 11.00 and 10.61 (10.63);
+// 32768 tokens 2.68 and 2.69.  Elsewhere bursts are as fast or faster: 128 x 128
+// 0.1-1 %.
+template <typename T, int D>
+constexpr bool kCopySpread = T::kWaves == 2 && D == 128;
+
 // Loads i0 .. i0 + count - 1 of a copy of rows key0 .. key0 + BK - 1 (rows sn
 // elements apart, row 0 at src + kCopyShift) into an LDS tile with global_load_lds_dwordx4 (no
 // registers; completion is tracked by vmcnt).  count and i0 are compile-time
@@ -182,7 +193,12 @@ __device__ __forceinline__ void issue_tile_slice(__bf16* lds, const __bf16* src,
 #pragma unroll
     for (int i = i0; i < i0 + count; i += step) {
       const char* from = tile + CopyPlan<T, D>::row_off(wave_u, i, sn);
-      if (step == 4)
+      if (step == 4 && kCopySpread<T, D>) {
+        copy16_to_lds<0, 1>(lds0 + i * 1024, from, cp.lane_off);
+        copy16_to_lds<1, 1>(lds0 + i * 1024, from, cp.lane_off);
+        copy16_to_lds<2, 1>(lds0 + i * 1024, from, cp.lane_off);
+        copy16_to_lds<3, 1>(lds0 + i * 1024, from, cp.lane_off);
+      } else if (step == 4)
         copy16_to_lds<0, 4>(lds0 + i * 1024, from, cp.lane_off);
       else if ((i & 3) == 0)
         copy16_to_lds<0, 2>(lds0 + i * 1024, from, cp.lane_off);
