@@ -663,7 +663,7 @@ __device__ __forceinline__ void merge_parts(f32x16 (&o)[D / 32], float& m, float
 // Beside another group's softmax it is 3195 -> 3113, +1.4 % maskless; with
 // masks and a full chip, clocked down by its power, it measured -1 to +0.5 %
 // and the plain form stays.  Items of 64 rows have no registers to spare: at
-// d = 64 it would cost them the second workgroup of a compute unit.
+// d = 64 it would cost maskless ones the second workgroup of a compute unit.
 template <int BQ, bool DENSE, int PARTS>
 constexpr bool kReadAhead = BQ == 128 && (DENSE || PARTS > 1);
 
